@@ -175,6 +175,14 @@ struct fsim_ctx {
     std::vector<double> Qkept[NPCLASS];
     bool screened = false;
     double tau = 0.0, tau32 = 0.0;
+    // pair order of the screen's kept pairs: class pc's element (cd, k) is at
+    // pj_off[pc] + cd * n + k; the density in that order (Dp), the matrix
+    // element each entry names (pj_src) and where each matrix element is
+    // (pj_pos, -1 for none).  At most packed entries in all: one per
+    // unordered pair of functions, and both orders within a shell.
+    long long pj_off[NPCLASS + 1] = {};
+    int *pj_src = nullptr, *pj_pos = nullptr;
+    double *Dp = nullptr;
     // primitive-pair screening threshold applied by the next screen (0: off)
     // and each kept pair's primitive pairs in use after it
     double tau_prim = 0.0;
@@ -1149,6 +1157,16 @@ extern "C" fsim_status fsim_schwarz_screen(fsim_ctx *c, double tau, double tau32
         }
         for (int v : np) S.prim_pairs_kept += v;
     }
+    for (int pc = 0; pc < NPCLASS; ++pc)
+        c->pj_off[pc + 1] = c->pj_off[pc] + (long long)c->kept[pc].n * ncart_h(pclass_l1(pc)) *
+                                                ncart_h(pclass_l2(pc));
+    HIPCHK(c->screen_pool.alloc(&c->pj_src, (size_t)c->pj_off[NPCLASS]));
+    HIPCHK(c->screen_pool.alloc(&c->Dp, (size_t)c->pj_off[NPCLASS]));
+    HIPCHK(c->screen_pool.alloc(&c->pj_pos, (size_t)c->packed));
+    HIPCHK(fill_int(c->pj_pos, (size_t)c->packed, -1, nullptr));
+    for (int pc = 0; pc < NPCLASS; ++pc)
+        HIPCHK(launch_pair_order(c->kept[pc], c->pj_off[pc], c->d_mol_off, c->d_mol_n, c->pj_src,
+                                 c->pj_pos, nullptr));
     // canonical quartets: per molecule, npair_m (npair_m + 1) / 2
     {
         std::vector<long long> np(c->nmol, 0);
@@ -1269,6 +1287,7 @@ extern "C" fsim_status fsim_schwarz_screen(fsim_ctx *c, double tau, double tau32
         S.quartets_fp64 = S.quartets_kept;
         S.quartets_fp32 = 0;
     }
+    HIPCHK(hipStreamSynchronize(nullptr));   // the pair-order maps, read on any stream
     c->tau = tau;
     c->tau32 = tau32;
     c->stats = S;
@@ -1332,12 +1351,12 @@ static fsim_status enqueue_build(fsim_ctx *c, const double *D, double *F, double
     double *Jsum = acc ? acc->J : c->Jh, *Ksum = acc ? acc->K : c->Kh;
     double *Jacc = xp ? c->priv : Jsum;
     double *Kacc = xp ? c->priv + NXCD * P : Ksum;
-    if (xp) {
-        HIPCHK(fill(c->priv, 2 * NXCD * P, 0.0, s));
-    } else {
-        HIPCHK(fill(Jsum, P, 0.0, s));
-        HIPCHK(fill(Ksum, P, 0.0, s));
-    }
+    // J' in pair order: the first PJ entries of each copy
+    const size_t PJ = (size_t)c->pj_off[NPCLASS];
+    if (xp)
+        HIPCHK(begin_build(c->priv, 2 * NXCD * P, nullptr, 0, PJ, c->pj_src, D, c->Dp, s));
+    else
+        HIPCHK(begin_build(Jsum, PJ, Ksum, P, PJ, c->pj_src, D, c->Dp, s));
     int nev = 0;
     // s/p classes through the persistent queue kernel when every one of them
     // fits its per-wave LDS stage (the stored-integral digest has its own kernel)
@@ -1379,7 +1398,9 @@ static fsim_status enqueue_build(fsim_ctx *c, const double *D, double *F, double
                     a.same_class = X == Y;
                     a.tl = tl;
                     a.D = D;
-                    a.Jh = Jacc;
+                    a.Dk = c->Dp + c->pj_off[Y];
+                    a.Jb = Jacc + c->pj_off[X];
+                    a.Jk = Jacc + c->pj_off[Y];
                     a.Kh = Kacc;
                     a.xcd_stride = xp ? (long long)P : 0;
                     a.nbf = c->nbf;
@@ -1413,7 +1434,9 @@ static fsim_status enqueue_build(fsim_ctx *c, const double *D, double *F, double
                 a.same_class = X == Y;
                 a.tl = tl;
                 a.D = D;
-                a.Jh = Jacc;
+                a.Dk = c->Dp + c->pj_off[Y];
+                a.Jb = Jacc + c->pj_off[X];
+                a.Jk = Jacc + c->pj_off[Y];
                 a.Kh = Kacc;
                 a.xcd_stride = xp ? (long long)P : 0;
                 a.nbf = c->nbf;
@@ -1483,13 +1506,12 @@ static fsim_status enqueue_build(fsim_ctx *c, const double *D, double *F, double
         if (prof) HIPCHK(hipEventRecord(c->ev[nev++], s));
     }
     if (xp) {
-        HIPCHK(sum_copies(P, NXCD, c->priv, P, Jsum, s));
-        HIPCHK(sum_copies(P, NXCD, c->priv + NXCD * P, P, Ksum, s));
+        HIPCHK(sum_copies2(NXCD, P, PJ, c->priv, Jsum, P, c->priv + NXCD * P, Ksum, s));
     }
     if (dref)
-        HIPCHK(assemble_delta(layout_of(c), Jsum, Ksum, c->H, dref->J, dref->K, F, J, K, s));
+        HIPCHK(assemble_delta(layout_of(c), Jsum, c->pj_pos, Ksum, c->H, dref->J, dref->K, F, J, K, s));
     else
-        HIPCHK(assemble_fock_packed(layout_of(c), Jsum, Ksum, c->H, F, J, K, s));
+        HIPCHK(assemble_fock_packed(layout_of(c), Jsum, c->pj_pos, Ksum, c->H, F, J, K, s));
     return FSIM_OK;
 }
 

@@ -153,9 +153,12 @@ struct EriArgs {
     // Fock mode
     TileList tl;
     const double *D;        // packed per-molecule blocks (one block for a single molecule)
-    double *Jh;
+    // in pair order (element (cd, k) of a class at cd * n + k, k the kept
+    // pair): the ket class's density and both classes' J' half-sums
+    const double *Dk;
+    double *Jb, *Jk;
     double *Kh;
-    // > 0: Jh and Kh each hold one copy per XCD, xcd_stride elements apart,
+    // > 0: J' and K' each hold one copy per XCD, xcd_stride elements apart,
     // and a wave adds into the copy of the XCD it runs on (0: one copy)
     long long xcd_stride;
     // lane kernels: each wave stages up to stage_prims primitive pairs of its
@@ -202,6 +205,10 @@ struct ShellsDev {
 hipError_t launch_shell_norm(const ShellsDev &sh, hipStream_t s);
 hipError_t launch_build_pairs(const ShellsDev &sh, PairTable &t, const int *pair_sh1,
                               const int *pair_sh2, hipStream_t s);
+// Index maps of one class's pair order (EriArgs): src[off + cd * n + k] is the
+// packed matrix element of component pair cd of pair k, pos the inverse.
+hipError_t launch_pair_order(const PairTable &t, long long off, const long long *mol_off,
+                             const int *mol_n, int *src, int *pos, hipStream_t s);
 // Drop the primitive pairs of every pair whose Schwarz bound times
 // qmax_mol[mol] is below tau_prim, compacting the slots in place (setup.hip).
 hipError_t launch_prim_screen(PairTable &t, const double *qmax_mol, double tau_prim,

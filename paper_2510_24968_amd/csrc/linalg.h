@@ -15,11 +15,12 @@ struct DiisPtrs {
 
 hipError_t fill(double *x, size_t n, double v, hipStream_t s);
 hipError_t fill_int(int *x, size_t n, int v, hipStream_t s);
-// dst[i] = sum_{k < ncopy} src[k * stride + i] for i < n
-hipError_t sum_copies(size_t n, int ncopy, const double *src, size_t stride, double *dst,
-                      hipStream_t s);
-hipError_t assemble_fock(int N, const double *Jh, const double *Kh, const double *H, double *F,
-                         double *J, double *K, hipStream_t s);
+// z0[0..n0) = z1[0..n1) = 0 and dst[i] = src[idx[i]] for i < n
+hipError_t begin_build(double *z0, size_t n0, double *z1, size_t n1, size_t n, const int *idx,
+                       const double *src, double *dst, hipStream_t s);
+// dK[i] = sum_{k < ncopy} sK[k * stride + i] for i < nK, K = 0, 1
+hipError_t sum_copies2(int ncopy, size_t stride, size_t n0, const double *s0, double *d0,
+                       size_t n1, const double *s1, double *d1, hipStream_t s);
 hipError_t dot3(size_t n, const double *A, const double *B, const double *C, double w, double *out,
                 hipStream_t s);
 hipError_t diff2(size_t n, const double *A, const double *B, double *out, hipStream_t s);
@@ -36,12 +37,15 @@ struct MolLayout {
     const long long *off = nullptr;   // [nmol]
     const int *n = nullptr;           // [nmol]
 };
-hipError_t assemble_fock_packed(const MolLayout &L, const double *Jh, const double *Kh,
+// J = J' + J'^T, K = Kh + Kh^T, F = H + J - K/2 per block; J' of matrix
+// element x is Jp[pos[x]] (0 where pos[x] < 0)
+hipError_t assemble_fock_packed(const MolLayout &L, const double *Jp, const int *pos,
+                                const double *Kh,
                                 const double *H, double *F, double *J, double *K, hipStream_t s);
-// J = Jref + Jh + Jh^T, K = Kref + Kh + Kh^T, F = H + J - K/2 per block (F may
+// J = Jref + J' + J'^T, K = Kref + Kh + Kh^T, F = H + J - K/2 per block (F may
 // be NULL; J may alias Jref, K may alias Kref)
-hipError_t assemble_delta(const MolLayout &L, const double *Jh, const double *Kh, const double *H,
-                          const double *Jref, const double *Kref, double *F, double *J, double *K,
+hipError_t assemble_delta(const MolLayout &L, const double *Jp, const int *pos,
+                          const double *Kh, const double *H, const double *Jref, const double *Kref, double *F, double *J, double *K,
                           hipStream_t s);
 // out = (A + A^T) / 2 (N x N; out must not alias A)
 hipError_t symmetrize(int N, const double *A, double *out, hipStream_t s);

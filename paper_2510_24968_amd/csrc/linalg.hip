@@ -15,28 +15,41 @@ __global__ void k_fill_int(int *x, size_t n, int v) {
         x[i] = v;
 }
 
-__global__ void k_sum_copies(size_t n, int ncopy, const double *__restrict__ src, size_t stride,
-                             double *dst) {
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n;
+// Start of a Fock build: both accumulators cleared and the density gathered
+// into pair order, in one launch (a small molecule's build is a few launches
+// of some 5 us each: 8 H atoms 93 -> 74 us with this and k_sum_copies2).
+__global__ void k_begin_build(double *z0, size_t n0, double *z1, size_t n1, size_t n,
+                              const int *__restrict__ idx, const double *__restrict__ src,
+                              double *__restrict__ dst) {
+    const size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
+    const size_t step = (size_t)gridDim.x * blockDim.x;
+    for (size_t i = t; i < n0; i += step) z0[i] = 0.0;
+    for (size_t i = t; i < n1; i += step) z1[i] = 0.0;
+    for (size_t i = t; i < n; i += step) dst[i] = src[idx[i]];
+}
+
+// dst[i] = sum of ncopy copies of src, for the J' (n0 elements) and K' (n1)
+// accumulators in one launch.
+__global__ void k_sum_copies2(int ncopy, size_t stride, size_t n0, const double *__restrict__ s0,
+                              double *__restrict__ d0, size_t n1, const double *__restrict__ s1,
+                              double *__restrict__ d1) {
+    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n0 + n1;
          i += (size_t)gridDim.x * blockDim.x) {
+        const bool first = i < n0;
+        const size_t x = first ? i : i - n0;
+        const double *__restrict__ src = first ? s0 : s1;
         double v = 0.0;
-        for (int k = 0; k < ncopy; ++k) v += src[k * stride + i];
-        dst[i] = v;
+        for (int k = 0; k < ncopy; ++k) v += src[k * stride + x];
+        (first ? d0 : d1)[x] = v;
     }
 }
 
-// J = J' + J'^T, K = K' + K'^T, F = H + J - K/2 (Eq. fock, G = J - K/2).
-__global__ void k_assemble_fock(int N, const double *__restrict__ Jh, const double *__restrict__ Kh,
-                                const double *__restrict__ H, double *F, double *J, double *K) {
-    const size_t n2 = (size_t)N * N;
-    for (size_t x = blockIdx.x * (size_t)blockDim.x + threadIdx.x; x < n2;
-         x += (size_t)gridDim.x * blockDim.x) {
-        const size_t i = x / N, j = x - i * N, xt = j * N + i;
-        const double jj = Jh[x] + Jh[xt], kk = Kh[x] + Kh[xt];
-        if (F) F[x] = H[x] + jj - 0.5 * kk;
-        if (J) J[x] = jj;
-        if (K) K[x] = kk;
-    }
+// J' of matrix element x from the pair-ordered sums: 0 where x names no
+// stored element (a dropped pair, or the transpose of a stored one).
+__device__ __forceinline__ double pair_value(const double *__restrict__ Jp,
+                                             const int *__restrict__ pos, size_t x) {
+    const int o = pos[x];
+    return o >= 0 ? Jp[o] : 0.0;
 }
 
 // Block-reduced sum of w * sum_x A[x] * (B[x] + C[x]) (C may be NULL) into *out.
@@ -114,8 +127,10 @@ __global__ void k_lincomb(size_t n, int m, DiisPtrs P, double *out) {
 // ---------------------------------------------------------------------------
 // packed / padded per-molecule kernels: grid.y runs over molecules
 // ---------------------------------------------------------------------------
-__global__ void k_assemble_packed(MolLayout L, const double *__restrict__ Jh,
-                                  const double *__restrict__ Kh, const double *__restrict__ H,
+// J = J' + J'^T, K = K' + K'^T, F = H + J - K/2 (Eq. fock, G = J - K/2), J'
+// in pair order (pos: where each matrix element's J' is kept, -1 if nowhere).
+__global__ void k_assemble_packed(MolLayout L, const double *__restrict__ Jp,
+                                  const int *__restrict__ pos, const double *__restrict__ Kh, const double *__restrict__ H,
                                   double *F, double *J, double *K) {
     const int m = blockIdx.y, n = L.n[m];
     const size_t base = L.off[m], n2 = (size_t)n * n;
@@ -123,7 +138,8 @@ __global__ void k_assemble_packed(MolLayout L, const double *__restrict__ Jh,
          x += (size_t)gridDim.x * blockDim.x) {
         const size_t i = x / n, j = x - i * n;
         const size_t a = base + x, at = base + j * n + i;
-        const double jj = Jh[a] + Jh[at], kk = Kh[a] + Kh[at];
+        const double jj = pair_value(Jp, pos, a) + pair_value(Jp, pos, at);
+        const double kk = Kh[a] + Kh[at];
         if (F) F[a] = H[a] + jj - 0.5 * kk;
         if (J) J[a] = jj;
         if (K) K[a] = kk;
@@ -132,8 +148,8 @@ __global__ void k_assemble_packed(MolLayout L, const double *__restrict__ Jh,
 
 // Incremental build: J = Jref + J'_d + J'_d^T, K = Kref + K'_d + K'_d^T,
 // F = H + J - K/2 (J may alias Jref and K may alias Kref).
-__global__ void k_assemble_delta(MolLayout L, const double *__restrict__ Jh,
-                                 const double *__restrict__ Kh, const double *__restrict__ H,
+__global__ void k_assemble_delta(MolLayout L, const double *__restrict__ Jp,
+                                 const int *__restrict__ pos, const double *__restrict__ Kh, const double *__restrict__ H,
                                  const double *Jref, const double *Kref, double *F, double *J,
                                  double *K) {
     const int m = blockIdx.y, n = L.n[m];
@@ -142,7 +158,8 @@ __global__ void k_assemble_delta(MolLayout L, const double *__restrict__ Jh,
          x += (size_t)gridDim.x * blockDim.x) {
         const size_t i = x / n, j = x - i * n;
         const size_t a = base + x, at = base + j * n + i;
-        const double jj = Jref[a] + (Jh[a] + Jh[at]), kk = Kref[a] + (Kh[a] + Kh[at]);
+        const double jj = Jref[a] + (pair_value(Jp, pos, a) + pair_value(Jp, pos, at));
+        const double kk = Kref[a] + (Kh[a] + Kh[at]);
         if (F) F[a] = H[a] + jj - 0.5 * kk;
         J[a] = jj;
         K[a] = kk;
@@ -332,10 +349,10 @@ static inline dim3 grid_mol(size_t per_mol, int nmol, int z = 1) {
     return dim3((unsigned)b, (unsigned)nmol, (unsigned)z);
 }
 
-hipError_t assemble_fock_packed(const MolLayout &L, const double *Jh, const double *Kh,
+hipError_t assemble_fock_packed(const MolLayout &L, const double *Jp, const int *pos, const double *Kh,
                                 const double *H, double *F, double *J, double *K, hipStream_t s) {
     hipLaunchKernelGGL(k_assemble_packed, grid_mol((size_t)L.nmax * L.nmax, L.nmol), dim3(256), 0,
-                       s, L, Jh, Kh, H, F, J, K);
+                       s, L, Jp, pos, Kh, H, F, J, K);
     return hipGetLastError();
 }
 hipError_t dot3_packed(const MolLayout &L, const double *A, const double *B, const double *C,
@@ -411,22 +428,26 @@ hipError_t fill_int(int *x, size_t n, int v, hipStream_t s) {
     hipLaunchKernelGGL(k_fill_int, grid_for(n), dim3(256), 0, s, x, n, v);
     return hipGetLastError();
 }
-hipError_t sum_copies(size_t n, int ncopy, const double *src, size_t stride, double *dst,
-                      hipStream_t s) {
-    hipLaunchKernelGGL(k_sum_copies, grid_for(n), dim3(256), 0, s, n, ncopy, src, stride, dst);
+hipError_t begin_build(double *z0, size_t n0, double *z1, size_t n1, size_t n, const int *idx,
+                       const double *src, double *dst, hipStream_t s) {
+    size_t most = n0 > n1 ? n0 : n1;
+    if (n > most) most = n;
+    hipLaunchKernelGGL(k_begin_build, grid_for(most), dim3(256), 0, s, z0, n0, z1, n1, n, idx, src,
+                       dst);
     return hipGetLastError();
 }
-hipError_t assemble_fock(int N, const double *Jh, const double *Kh, const double *H, double *F,
-                         double *J, double *K, hipStream_t s) {
-    hipLaunchKernelGGL(k_assemble_fock, grid_for((size_t)N * N), dim3(256), 0, s, N, Jh, Kh, H, F,
-                       J, K);
+hipError_t sum_copies2(int ncopy, size_t stride, size_t n0, const double *s0, double *d0,
+                       size_t n1, const double *s1, double *d1, hipStream_t s) {
+    hipLaunchKernelGGL(k_sum_copies2, grid_for(n0 + n1), dim3(256), 0, s, ncopy, stride, n0, s0,
+                       d0, n1, s1, d1);
     return hipGetLastError();
 }
-hipError_t assemble_delta(const MolLayout &L, const double *Jh, const double *Kh, const double *H,
+hipError_t assemble_delta(const MolLayout &L, const double *Jp, const int *pos,
+                          const double *Kh, const double *H,
                           const double *Jref, const double *Kref, double *F, double *J, double *K,
                           hipStream_t s) {
     hipLaunchKernelGGL(k_assemble_delta, grid_mol((size_t)L.nmax * L.nmax, L.nmol), dim3(256), 0,
-                       s, L, Jh, Kh, H, Jref, Kref, F, J, K);
+                       s, L, Jp, pos, Kh, H, Jref, Kref, F, J, K);
     return hipGetLastError();
 }
 hipError_t symmetrize(int N, const double *A, double *out, hipStream_t s) {

@@ -177,6 +177,30 @@ __global__ void k_build_pairs(ShellsDev sh, PairTable t, const int *__restrict__
     }
 }
 
+// Pair order of one class (element (cd, k) at off + cd * n + k): src names
+// each element's place in the packed matrices, pos the inverse.
+__global__ void k_pair_order(PairTable t, int n1, int n2, long long off,
+                             const long long *__restrict__ mol_off,
+                             const int *__restrict__ mol_n, int *__restrict__ src,
+                             int *__restrict__ pos) {
+    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
+    if (idx >= t.n * n1 * n2) return;
+    const int k = idx % t.n, cd = idx / t.n;
+    const int m = t.mol[k];
+    const long long x = mol_off[m] + (long long)(t.bf1[k] + cd / n2) * mol_n[m] + t.bf2[k] + cd % n2;
+    src[off + idx] = (int)x;
+    pos[x] = (int)(off + idx);
+}
+
+hipError_t launch_pair_order(const PairTable &t, long long off, const long long *mol_off,
+                             const int *mol_n, int *src, int *pos, hipStream_t s) {
+    if (t.n == 0) return hipSuccess;
+    const int n1 = ncart(t.l1), n2 = ncart(t.l2);
+    hipLaunchKernelGGL(k_pair_order, dim3((t.n * n1 * n2 + 255) / 256), dim3(256), 0, s, t, n1, n2,
+                       off, mol_off, mol_n, src, pos);
+    return hipGetLastError();
+}
+
 hipError_t launch_build_pairs(const ShellsDev &sh, PairTable &t, const int *ps1, const int *ps2,
                               hipStream_t s) {
     if (t.n == 0) return hipSuccess;

@@ -56,7 +56,10 @@ __global__ __launch_bounds__(SEG ? 512 : 256) void k_digest_stored(EriArgs a) {
         const long long mbase = a.mol_off[mol];
         const int N = a.mol_n[mol];
         const double *__restrict__ D = a.D + mbase;
-        double *__restrict__ Jh = a.Jh + xoff + mbase;
+        const size_t nb = a.bra.n, nk = a.ket.n;
+        const double *__restrict__ Dk = a.Dk + ket;
+        double *__restrict__ Jb = a.Jb + xoff + bra;
+        double *__restrict__ Jk = a.Jk + xoff + ket;
         double *__restrict__ Kh = a.Kh + xoff + mbase;
         const int f1 = __builtin_amdgcn_readfirstlane(a.bra.bf1[bra]);
         const int f2 = __builtin_amdgcn_readfirstlane(a.bra.bf2[bra]);
@@ -81,9 +84,8 @@ __global__ __launch_bounds__(SEG ? 512 : 256) void k_digest_stored(EriArgs a) {
                     out[abl][cdl] = active ? src[(size_t)e * 64] : 0.0;
                 });
             });
-            digest_chunk<LA, LB, LC, LD, double, A0, A1, CD0, CD1>(out, D, Jh, Kh, N, f1, f2, f3,
-                                                                   f4, fac, active, krow, a.kn,
-                                                                   kl);
+            digest_chunk<LA, LB, LC, LD, double, A0, A1, CD0, CD1>(
+                out, D, Dk, Jb, Jk, nb, nk, Kh, N, f1, f2, f3, f4, fac, active, krow, a.kn, kl);
         });
     };
     if constexpr (SEG) {
