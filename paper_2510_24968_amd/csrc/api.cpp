@@ -284,6 +284,9 @@ static fsim_status alloc_table(DevPool &pool, PairTable &t, int l1, int l2, int 
     HIPCHK(pool.alloc(&t.P, (size_t)kmax * 3 * n));
     HIPCHK(pool.alloc(&t.E, (size_t)kmax * t.ne * n));
     HIPCHK(pool.alloc(&t.Ef, (size_t)kmax * t.ne * n));
+    HIPCHK(pool.alloc(&t.rp, (size_t)kmax * 4 * n));
+    HIPCHK(pool.alloc(&t.rE, (size_t)kmax * t.ne * n));
+    HIPCHK(pool.alloc(&t.rEf, (size_t)kmax * t.ne * n));
     return FSIM_OK;
 }
 
@@ -301,6 +304,7 @@ static fsim_status build_table(fsim_ctx *c, DevPool &pool, PairTable &t, int pc,
     HIPCHK(hipMemcpy(d1, s1.data(), sizeof(int) * t.n, hipMemcpyHostToDevice));
     HIPCHK(hipMemcpy(d2, s2.data(), sizeof(int) * t.n, hipMemcpyHostToDevice));
     HIPCHK(launch_build_pairs(c->sh, t, d1, d2, nullptr));
+    HIPCHK(launch_pack_rows(t, nullptr));
     HIPCHK(hipDeviceSynchronize());
     hipFree(d1);
     hipFree(d2);
@@ -1150,6 +1154,7 @@ extern "C" fsim_status fsim_schwarz_screen(fsim_ctx *c, double tau, double tau32
             HIPCHK(hipMalloc(&dq, sizeof(double) * c->nmol));
             HIPCHK(hipMemcpy(dq, Qmax.data(), sizeof(double) * c->nmol, hipMemcpyHostToDevice));
             HIPCHK(launch_prim_screen(c->kept[pc], dq, c->tau_prim, nullptr));
+            HIPCHK(launch_pack_rows(c->kept[pc], nullptr));   // the slots moved
             HIPCHK(hipDeviceSynchronize());
             hipFree(dq);
             HIPCHK(hipMemcpy(np.data(), c->kept[pc].nprim, sizeof(int) * np.size(),
@@ -1328,7 +1333,6 @@ static int persist_slot_of(int X, int Y) {
     return -1;
 }
 static constexpr int PERSIST_PROFILE_CLASS = NPCLASS;
-static constexpr int KO_STAGE_BYTES_MAX = 8192;   // per-wave LDS stage of a ket-outer tile
 
 // acc (optional): one shared pair of J'/K' accumulators to use instead of
 // the context's own (the allocation-free entry point).
@@ -1358,19 +1362,9 @@ static fsim_status enqueue_build(fsim_ctx *c, const double *D, double *F, double
     else
         HIPCHK(begin_build(Jsum, PJ, Ksum, P, PJ, c->pj_src, D, c->Dp, s));
     int nev = 0;
-    // s/p classes through the persistent queue kernel when every one of them
-    // fits its per-wave LDS stage (the stored-integral digest has its own kernel)
-    int pstage = 0;
-    bool persist = c->persistent && !(c->stored && !dref);
-    if (persist) {
-        for (int k = 0; k < PERSIST_SLOTS; ++k) {
-            const int X = persist_slot_bra(k);
-            const int per_prim = 32 + n_entries(pclass_l1(X), pclass_l2(X)) * 8;   // FP64 boxes
-            const int bytes = std::max(1, c->kept[X].kmax) * per_prim;
-            pstage = std::max(pstage, (bytes + 15) / 16 * 16);
-        }
-        persist = pstage <= KO_STAGE_BYTES_MAX;
-    }
+    // s/p classes through the persistent queue kernel (the stored-integral
+    // digest has its own kernel)
+    const bool persist = c->persistent && !(c->stored && !dref);
     PersistArgs pa[2];
     bool have_pa[2] = {false, false};
     const int maxn = *std::max_element(c->mol_n.begin(), c->mol_n.end());
@@ -1407,8 +1401,6 @@ static fsim_status enqueue_build(fsim_ctx *c, const double *D, double *F, double
                     a.mol_off = c->d_mol_off;
                     a.mol_n = c->d_mol_n;
                     a.boys = c->boys;
-                    a.stage_prims = std::max(1, c->kept[X].kmax);
-                    a.stage_bytes = pstage;
                     continue;
                 }
                 if (tl.ntile == 0) continue;
@@ -1487,7 +1479,6 @@ static fsim_status enqueue_build(fsim_ctx *c, const double *D, double *F, double
         }
         if (q.start[PERSIST_SLOTS] == 0) continue;
         q.counter = c->pcounter + part;
-        q.stage_bytes = pstage;
         q.boys = c->boys;
         if (prof) {
             fsim_class_profile pr{};

@@ -47,6 +47,23 @@ __device__ __forceinline__ const double *etab<double>(const PairTable &t) { retu
 template <>
 __device__ __forceinline__ const float *etab<float>(const PairTable &t) { return t.Ef; }
 
+template <typename T>
+__device__ __forceinline__ const T *rtab(const PairTable &t);
+template <>
+__device__ __forceinline__ const double *rtab<double>(const PairTable &t) { return t.rE; }
+template <>
+__device__ __forceinline__ const float *rtab<float>(const PairTable &t) { return t.rEf; }
+
+// Pointers into the constant address space: loads at wave-uniform addresses
+// become scalar loads into SGPRs, which the VALU takes as operands.  Only for
+// tables no kernel of the launch writes.
+template <typename T>
+using ConstPtr = const __attribute__((address_space(4))) T *;
+template <typename T>
+__device__ __forceinline__ ConstPtr<T> const_ptr(const T *p) {
+    return (ConstPtr<T>)(unsigned long long)p;
+}
+
 // Index (0..7) of the XCD the calling wave runs on, from the XCC_ID
 // hardware register (bits 3:0).
 __device__ __forceinline__ int xcd_index() {
@@ -647,8 +664,9 @@ __global__ __launch_bounds__(SEG ? 64 * seg_waves(LA, LB, LC, LD, CA, CDC) : 256
 // Kernel A, ket-outer order (ss, ps, pp and ds bras; Fock or store mode).  The same lane-per-
 // quartet tiles as k_eri_lane, with the primitive loops swapped: each ket
 // primitive's data are loaded once and held in registers while the bra
-// primitives (staged in LDS for the whole wave) run inside, and the bra
-// contraction is applied per primitive quartet:
+// primitives (wave-uniform, read by scalar loads from the row tables; staged
+// in LDS they cost the 64-water s/p build 312 ms against 292) run inside, and
+// the bra contraction is applied per primitive quartet:
 //   V_{tuv,cd} = sum_{tau nu phi} (-1)^{tau+nu+phi} E^{cd}_{tau nu phi} R^0_{t+tau,u+nu,v+phi}
 //   (ab|cd)   += sum_tuv E^{ab}_{tuv} V_{tuv,cd}
 // This trades the once-per-bra-primitive bra step for one per primitive
@@ -672,13 +690,10 @@ struct BoysStagedMixed {
     }
 };
 
-// One tile (one bra pair x up to 64 kets) of the ket-outer kernel.  sp: this
-// wave's LDS slice for the staged bra primitives (4 + n_entries values each,
-// a.stage_prims of them).
+// One tile (one bra pair x up to 64 kets) of the ket-outer kernel.
 template <int LA, int LB, int LC, int LD, typename T, bool STORE, int CA, int CDC, typename BP>
 __device__ __forceinline__ void ko_tile(const EriArgs &a, const int tile, const BP &bp,
-                                        double *__restrict__ sp, double *__restrict__ krow = nullptr,
-                                        bool kl = false) {
+                                        double *__restrict__ krow = nullptr, bool kl = false) {
     constexpr int L = LA + LB + LC + LD, LAB = LA + LB;
     constexpr int NA = ncart(LA), NB = ncart(LB), NC = ncart(LC), ND = ncart(LD);
     constexpr int NCD = NC * ND, NHAB = nherm(LAB), NH = nherm(L);
@@ -686,11 +701,9 @@ __device__ __forceinline__ void ko_tile(const EriArgs &a, const int tile, const 
     constexpr int NCHA = (NA + CA - 1) / CA, NCHCD = (NCD + CDC - 1) / CDC;
     constexpr bool F32 = std::is_same<T, float>::value;
     const int lane = threadIdx.x & 63;
-    const T *__restrict__ Eb = etab<T>(a.bra);
     const T *__restrict__ Ek = etab<T>(a.ket);
     const size_t nb = a.bra.n, nk = a.ket.n;
     const long long xoff = (!STORE && a.xcd_stride) ? xcd_index() * a.xcd_stride : 0;
-    T *__restrict__ se = (T *)(sp + 4 * a.stage_prims);
     int bra, ket;
     bool active;
     if constexpr (STORE) {
@@ -736,15 +749,9 @@ __device__ __forceinline__ void ko_tile(const EriArgs &a, const int tile, const 
         }
     }
 
-    // stage the bra primitives: p, P (4 doubles) and the Hermite boxes
-    for (int x = lane; x < nbp * 4; x += 64) {
-        const int s = x >> 2, f = x & 3;
-        sp[x] = f == 0 ? a.bra.p[(size_t)s * nb + bra] : a.bra.P[((size_t)s * 3 + f - 1) * nb + bra];
-    }
-    for (int x = lane; x < nbp * NEB; x += 64) se[x] = Eb[(size_t)x * nb + bra];
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    // the bra's primitive rows
+    const ConstPtr<double> rp = const_ptr(a.bra.rp + (size_t)bra * a.bra.kmax * 4);
+    const ConstPtr<T> re = const_ptr(rtab<T>(a.bra) + (size_t)bra * a.bra.kmax * NEB);
 
     static_for<NCHA * NCHCD>([&](auto ch_) {
         constexpr int ch = decltype(ch_)::value;
@@ -773,19 +780,9 @@ __device__ __forceinline__ void ko_tile(const EriArgs &a, const int tile, const 
                 ek[e - EK0] = ev;
             }
             for (int i = 0; i < nbp; ++i) {
-                // bras with small Hermite boxes (ss, ps) read this
-                // primitive's box entries here, in one batch with its p and
-                // P, instead of one LDS round trip per pair of entries in
-                // the bra step below
-                constexpr bool EPRE = NEB <= 8;
-                T ebr[EPRE ? NEB : 1];
-                if constexpr (EPRE) {
-#pragma unroll
-                    for (int e = 0; e < NEB; ++e) ebr[e] = se[i * NEB + e];
-                }
-                const double p = sp[i * 4 + 0];
-                const double X = sp[i * 4 + 1] - Kx, Y = sp[i * 4 + 2] - Ky,
-                             Z = sp[i * 4 + 3] - Kz;
+                const double p = rp[i * 4 + 0];
+                const double X = rp[i * 4 + 1] - Kx, Y = rp[i * 4 + 2] - Ky,
+                             Z = rp[i * 4 + 3] - Kz;
                 T src[L + 1];
                 if constexpr (F32) {
                     // FP32 tile: FP32 Taylor step, FP64 recursion and
@@ -842,8 +839,8 @@ __device__ __forceinline__ void ko_tile(const EriArgs &a, const int tile, const 
                         });
                     });
                 });
-                // bra step for this primitive quartet (boxes from LDS)
-                const T *__restrict__ eb = se + i * NEB;
+                // bra step for this primitive quartet
+                const ConstPtr<T> eb = re + i * NEB;
                 static_for<NABc>([&](auto abl_) {
                     constexpr int abl = decltype(abl_)::value;
                     constexpr int ab = (A0 + abl / NB) * NB + abl % NB;
@@ -857,7 +854,7 @@ __device__ __forceinline__ void ko_tile(const EriArgs &a, const int tile, const 
                             static_for<az + 1>([&](auto v_) {
                                 constexpr int v = decltype(v_)::value;
                                 constexpr int e = ao + (t * (ay + 1) + u) * (az + 1) + v;
-                                const T ebv = EPRE ? ebr[EPRE ? e : 0] : eb[e];
+                                const T ebv = eb[e];
                                 static_for<NCDc>([&](auto cdl_) {
                                     constexpr int cdl = decltype(cdl_)::value;
                                     out[abl][cdl] = fma(ebv, V[cdl][hidx(t, u, v)], out[abl][cdl]);
@@ -911,29 +908,27 @@ void k_eri_lane_ko(EriArgs a) {
     constexpr bool ET = !F32 && LA <= 1 && SEG;
     __shared__ std::conditional_t<F32, float, double>
         tab[F32 ? BOYS_LDS32 : (ET ? BOYS_LDS_E : BOYS_LDS)];
-    extern __shared__ __align__(16) unsigned char stage_lds[];
+    extern __shared__ __align__(16) unsigned char row_lds[];
     if constexpr (F32) boys_stage32(tab, a.boys, L);
     else boys_stage(tab, a.boys, L);
     if constexpr (ET) boys_stage_exp(tab);
     __syncthreads();
     const int wpb = blockDim.x >> 6;
     const int ntile = STORE ? a.st_ntile : a.tl.ntile;
-    // every bra primitive of the tile is staged (the launch checks kmax fits)
-    double *__restrict__ sp = (double *)(stage_lds + (size_t)(threadIdx.x >> 6) * a.stage_bytes);
     using BP = std::conditional_t<F32, BoysStagedMixed, BoysStaged64<ET>>;
     const BP bp{tab};
     if constexpr (SEG && !STORE) {
         // segment mode: the block's waves share the bra's K' rows
-        double *__restrict__ krow = (double *)(stage_lds + (size_t)wpb * a.stage_bytes);
+        double *__restrict__ krow = (double *)row_lds;
         const long long xoff = a.xcd_stride ? xcd_index() * a.xcd_stride : 0;
         run_segments<ncart(LA), ncart(LB)>(a, krow, xoff, [&](int t) __attribute__((always_inline)) {
-            ko_tile<LA, LB, LC, LD, T, STORE, CA, CDC>(a, t, bp, sp, krow, true);
+            ko_tile<LA, LB, LC, LD, T, STORE, CA, CDC>(a, t, bp, krow, true);
         });
     } else {
         for (int tile0 = blockIdx.x * wpb + (threadIdx.x >> 6); tile0 < ntile;
              tile0 += gridDim.x * wpb)
             ko_tile<LA, LB, LC, LD, T, STORE, CA, CDC>(a, __builtin_amdgcn_readfirstlane(tile0),
-                                                       bp, sp);
+                                                       bp);
     }
 }
 
@@ -1596,10 +1591,8 @@ __host__ __device__ constexpr int variant_budget(int v) {
 }
 constexpr int MAX_CHUNKS = 24;
 
-// LDS per wave for the staged bra primitives of the lane kernel, and the
-// most the ket-outer kernel may stage (all primitives of the bra)
+// LDS per wave for the staged bra primitives of the bra-outer lane kernel
 constexpr int STAGE_BYTES = 3072;
-constexpr int KO_STAGE_MAX = 8192;
 // the ket-outer kernel serves bra classes with small Hermite boxes (ss, ps,
 // pp, ds: 1, 6, 33, 21 entries), whose per-quartet bra step is cheap
 constexpr int KO_MAX_BRA_BOX = 33;
@@ -1689,35 +1682,29 @@ void launch_ko(int ntile, int wpb, const EriArgs &a, hipStream_t s) {
     constexpr int BUDGET = variant_budget(DEFAULT_VARIANT);
     if constexpr (n_entries(LA, LB) <= KO_MAX_BRA_BOX && lane_fits<LA, LB, LC, LD, BUDGET>()) {
         constexpr int CA = chunk_a(LA, LB, LC, LD, BUDGET), CDC = chunk_cd(LA, LB, LC, LD, BUDGET);
-        constexpr int per_prim = 4 * (int)sizeof(double) + n_entries(LA, LB) * (int)sizeof(T);
-        const int kmax = a.bra.kmax > 0 ? a.bra.kmax : 1;
-        if (kmax * per_prim <= KO_STAGE_MAX) {
-            EriArgs b = a;
-            b.stage_prims = kmax;
-            b.stage_bytes = (kmax * per_prim + 15) / 16 * 16;
-            if constexpr (!STORE) {
-                if (wpb == 8) {
-                    auto seg = k_eri_lane_ko<LA, LB, LC, LD, T, false, CA, CDC, true>;
-                    constexpr int W =
-                        ko_seg_waves(LA, LB, LC, LD, !std::is_same<T, float>::value);
-                    int sblocks = 0;
-                    size_t dyn = 0;
-                    if (segment_fit<LA, LB>((const void *)seg, W, b, sblocks, dyn)) {
-                        hipLaunchKernelGGL(seg, dim3(sblocks), dim3(64 * W), dyn, s, b);
-                        return;
-                    }
+        EriArgs b = a;
+        b.stage_prims = b.stage_bytes = 0;
+        if constexpr (!STORE) {
+            if (wpb == 8) {
+                auto seg = k_eri_lane_ko<LA, LB, LC, LD, T, false, CA, CDC, true>;
+                constexpr int W = ko_seg_waves(LA, LB, LC, LD, !std::is_same<T, float>::value);
+                int sblocks = 0;
+                size_t dyn = 0;
+                if (segment_fit<LA, LB>((const void *)seg, W, b, sblocks, dyn)) {
+                    hipLaunchKernelGGL(seg, dim3(sblocks), dim3(64 * W), dyn, s, b);
+                    return;
                 }
             }
-            b.kn = 0;
-            const int w = wpb > 4 ? 4 : wpb;
-            int blocks = (ntile + w - 1) / w;
-            if (blocks > 8192) blocks = 8192;
-            hipLaunchKernelGGL((k_eri_lane_ko<LA, LB, LC, LD, T, STORE, CA, CDC, false>),
-                               dim3(blocks), dim3(64 * w), (size_t)w * b.stage_bytes, s, b);
-            return;
         }
+        b.kn = 0;
+        const int w = wpb > 4 ? 4 : wpb;
+        int blocks = (ntile + w - 1) / w;
+        if (blocks > 8192) blocks = 8192;
+        hipLaunchKernelGGL((k_eri_lane_ko<LA, LB, LC, LD, T, STORE, CA, CDC, false>), dim3(blocks),
+                           dim3(64 * w), 0, s, b);
+    } else {
+        launch_budget<LA, LB, LC, LD, T, STORE, BUDGET>(ntile, wpb, a, s);
     }
-    launch_budget<LA, LB, LC, LD, T, STORE, BUDGET>(ntile, wpb, a, s);
 }
 
 // One variant in Fock mode (STORE = false) or store mode (the same kernel

@@ -125,6 +125,11 @@ struct PairTable {
     double *P = nullptr;                  // [kmax][3][n]
     double *E = nullptr;                  // [kmax][ne][n]
     float *Ef = nullptr;                  // FP32 copy of E
+    // the same primitive data row by row, for the bra side, where a whole
+    // wave reads one pair's rows (scalar loads)
+    double *rp = nullptr;                 // [n][kmax][4]: p, P
+    double *rE = nullptr;                 // [n][kmax][ne]
+    float *rEf = nullptr;                 // FP32 copy of rE
 };
 
 // Tile lists of one quartet class and precision: bra pair b owns the ket
@@ -161,8 +166,8 @@ struct EriArgs {
     // > 0: J' and K' each hold one copy per XCD, xcd_stride elements apart,
     // and a wave adds into the copy of the XCD it runs on (0: one copy)
     long long xcd_stride;
-    // lane kernels: each wave stages up to stage_prims primitive pairs of its
-    // bra (p, P, Hermite boxes) in stage_bytes of dynamic LDS
+    // bra-outer lane kernels: each wave stages up to stage_prims primitive
+    // pairs of its d bra (p, P, Hermite boxes) in stage_bytes of dynamic LDS
     int stage_prims, stage_bytes;
     int nbf;
     const long long *mol_off;   // [nmol] offset of each molecule's N_m x N_m block
@@ -209,6 +214,8 @@ hipError_t launch_build_pairs(const ShellsDev &sh, PairTable &t, const int *pair
 // packed matrix element of component pair cd of pair k, pos the inverse.
 hipError_t launch_pair_order(const PairTable &t, long long off, const long long *mol_off,
                              const int *mol_n, int *src, int *pos, hipStream_t s);
+// Fill the row copies rp, rE, rEf from the columns (setup.hip).
+hipError_t launch_pack_rows(const PairTable &t, hipStream_t s);
 // Drop the primitive pairs of every pair whose Schwarz bound times
 // qmax_mol[mol] is below tau_prim, compacting the slots in place (setup.hip).
 hipError_t launch_prim_screen(PairTable &t, const double *qmax_mol, double tau_prim,
@@ -223,15 +230,13 @@ hipError_t launch_eri_unit(bool store, int variant, int wpb, const EriArgs &a, h
 // slot k holds the tiles (or segments) of class (persist_bra(k) | persist_ket(k)), slots
 // 0..5 = (pp|pp) (pp|ps) (ps|ps) (pp|ss) (ps|ss) (ss|ss); start[k] is the
 // first queue position of slot k, start[6] the total.  *counter must be 0
-// at launch.  Every slot's stage_prims x (4 + n_entries) FP64/T values must
-// fit stage_bytes, the per-wave LDS slice.
+// at launch.
 constexpr int PERSIST_SLOTS = 6;
 constexpr int PERSIST_BUDGET = 128;   // lane-kernel live-value budget of the tile bodies
 struct PersistArgs {
     EriArgs cls[PERSIST_SLOTS];
     int start[PERSIST_SLOTS + 1];
     int *counter;
-    int stage_bytes;
     const double *boys;
     // > 0: queue items are segments (start[] counts segments), each taken
     // by a whole block that keeps its bra's K' rows in LDS (kn doubles per

@@ -77,20 +77,19 @@ __host__ __device__ constexpr int persist_ket(int slot) {
 }
 
 template <int SLOT, typename T, typename BP>
-__device__ __forceinline__ void persist_tile(const PersistArgs &p, int tile, const BP &bp,
-                                             double *sp) {
+__device__ __forceinline__ void persist_tile(const PersistArgs &p, int tile, const BP &bp) {
     constexpr int X = persist_bra(SLOT), Y = persist_ket(SLOT);
     constexpr int LA = pc_l1(X), LB = pc_l2(X), LC = pc_l1(Y), LD = pc_l2(Y);
     constexpr int B = PERSIST_BUDGET;
     ko_tile<LA, LB, LC, LD, T, false, chunk_a(LA, LB, LC, LD, B), chunk_cd(LA, LB, LC, LD, B)>(
-        p.cls[SLOT], tile, bp, sp);
+        p.cls[SLOT], tile, bp);
 }
 
 // Segment item: the block's waves split the segment's tiles, adding K' into
 // the LDS rows, which are flushed once the block is done with it.
 template <int SLOT, typename T, typename BP>
 __device__ __forceinline__ void persist_segment(const PersistArgs &p, int sg, const BP &bp,
-                                                double *sp, double *krow) {
+                                                double *krow) {
     constexpr int X = persist_bra(SLOT), Y = persist_ket(SLOT);
     constexpr int LA = pc_l1(X), LB = pc_l2(X), LC = pc_l1(Y), LD = pc_l2(Y);
     constexpr int B = PERSIST_BUDGET;
@@ -99,7 +98,7 @@ __device__ __forceinline__ void persist_segment(const PersistArgs &p, int sg, co
     const int t0 = a.tl.seg_t0[sg], nt = a.tl.seg_nt[sg];
     for (int t = t0 + wave; t < t0 + nt; t += wpb)
         ko_tile<LA, LB, LC, LD, T, false, chunk_a(LA, LB, LC, LD, B), chunk_cd(LA, LB, LC, LD, B)>(
-            a, __builtin_amdgcn_readfirstlane(t), bp, sp, krow, true);
+            a, __builtin_amdgcn_readfirstlane(t), bp, krow, true);
     __syncthreads();
     const long long xoff = a.xcd_stride ? xcd_index() * a.xcd_stride : 0;
     segment_flush<ncart(LA), ncart(LB)>(a, krow, xoff, sg);
@@ -111,19 +110,18 @@ __global__ __launch_bounds__(256, 2) void k_eri_persistent(PersistArgs p) {
     constexpr bool F32 = std::is_same<T, float>::value;
     constexpr int NR = F32 ? PERSIST_NR32 : PERSIST_NR;
     __shared__ std::conditional_t<F32, float, double> tab[BOYS_NT * NR];
-    extern __shared__ __align__(16) unsigned char stage_lds[];
+    extern __shared__ __align__(16) unsigned char row_lds[];
     for (int i = threadIdx.x; i < BOYS_NT * NR; i += blockDim.x)
         tab[i] = p.boys[(i / NR) * BOYS_NORD + i % NR];
     __syncthreads();
     const int lane = threadIdx.x & 63;
-    double *__restrict__ sp = (double *)(stage_lds + (size_t)(threadIdx.x >> 6) * p.stage_bytes);
     using BP = std::conditional_t<F32, BoysRawMixed, BoysRaw64>;
     const BP bp{tab};
     const int total = p.start[PERSIST_SLOTS];
     if (p.kn > 0) {
-        // segment items, one per block at a time; the rows (6 of kn doubles,
-        // the pp bras' count) follow the 4 staging slices
-        double *__restrict__ krow = (double *)(stage_lds + (size_t)4 * p.stage_bytes);
+        // segment items, one per block at a time, with 6 rows of kn doubles
+        // (the pp bras' count)
+        double *__restrict__ krow = (double *)row_lds;
         __shared__ int item;
         for (int x = threadIdx.x; x < 6 * p.kn; x += blockDim.x) krow[x] = 0.0;
         while (true) {
@@ -136,12 +134,12 @@ __global__ __launch_bounds__(256, 2) void k_eri_persistent(PersistArgs p) {
             while (slot + 1 < PERSIST_SLOTS && q >= p.start[slot + 1]) ++slot;
             const int sg = q - p.start[slot];
             switch (slot) {
-                case 0: persist_segment<0, T>(p, sg, bp, sp, krow); break;
-                case 1: persist_segment<1, T>(p, sg, bp, sp, krow); break;
-                case 2: persist_segment<2, T>(p, sg, bp, sp, krow); break;
-                case 3: persist_segment<3, T>(p, sg, bp, sp, krow); break;
-                case 4: persist_segment<4, T>(p, sg, bp, sp, krow); break;
-                default: persist_segment<5, T>(p, sg, bp, sp, krow); break;
+                case 0: persist_segment<0, T>(p, sg, bp, krow); break;
+                case 1: persist_segment<1, T>(p, sg, bp, krow); break;
+                case 2: persist_segment<2, T>(p, sg, bp, krow); break;
+                case 3: persist_segment<3, T>(p, sg, bp, krow); break;
+                case 4: persist_segment<4, T>(p, sg, bp, krow); break;
+                default: persist_segment<5, T>(p, sg, bp, krow); break;
             }
         }
         return;
@@ -155,12 +153,12 @@ __global__ __launch_bounds__(256, 2) void k_eri_persistent(PersistArgs p) {
         while (slot + 1 < PERSIST_SLOTS && q >= p.start[slot + 1]) ++slot;
         const int tile = q - p.start[slot];
         switch (slot) {
-            case 0: persist_tile<0, T>(p, tile, bp, sp); break;
-            case 1: persist_tile<1, T>(p, tile, bp, sp); break;
-            case 2: persist_tile<2, T>(p, tile, bp, sp); break;
-            case 3: persist_tile<3, T>(p, tile, bp, sp); break;
-            case 4: persist_tile<4, T>(p, tile, bp, sp); break;
-            default: persist_tile<5, T>(p, tile, bp, sp); break;
+            case 0: persist_tile<0, T>(p, tile, bp); break;
+            case 1: persist_tile<1, T>(p, tile, bp); break;
+            case 2: persist_tile<2, T>(p, tile, bp); break;
+            case 3: persist_tile<3, T>(p, tile, bp); break;
+            case 4: persist_tile<4, T>(p, tile, bp); break;
+            default: persist_tile<5, T>(p, tile, bp); break;
         }
     }
 }
@@ -169,12 +167,11 @@ hipError_t launch_persistent(bool fp32, const PersistArgs &pin, hipStream_t s) {
     if (pin.start[PERSIST_SLOTS] <= 0) return hipSuccess;
     PersistArgs p = pin;
     if (p.kn > 0) {
-        // segment items need the rows beside the Boys grid and the staging
-        // slices; otherwise tile items with global K' atomics
+        // segment items need the rows beside the Boys grid; otherwise tile
+        // items with global K' atomics
         const size_t stat = (size_t)BOYS_NT * (fp32 ? PERSIST_NR32 * sizeof(float)
                                                     : PERSIST_NR * sizeof(double));
-        const size_t need_lds =
-            stat + (size_t)4 * p.stage_bytes + (size_t)6 * p.kn * sizeof(double);
+        const size_t need_lds = stat + (size_t)6 * p.kn * sizeof(double);
         if (need_lds > LDS_PER_CU) {
             p.kn = 0;
             for (int k = 0; k < PERSIST_SLOTS; ++k) {
@@ -191,7 +188,7 @@ hipError_t launch_persistent(bool fp32, const PersistArgs &pin, hipStream_t s) {
     if (e != hipSuccess) return e;
     e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
     if (e != hipSuccess) return e;
-    const size_t dyn = (size_t)4 * p.stage_bytes + (size_t)6 * p.kn * sizeof(double);
+    const size_t dyn = (size_t)6 * p.kn * sizeof(double);
     int per_cu = 0;
     if (cached[fp32][0] == (int)dyn && cached[fp32][1] > 0) {
         per_cu = cached[fp32][1];

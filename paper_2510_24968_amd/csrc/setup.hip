@@ -177,6 +177,34 @@ __global__ void k_build_pairs(ShellsDev sh, PairTable t, const int *__restrict__
     }
 }
 
+// Row copies of the primitive data, one thread per (pair, slot, entry), the
+// four of p and P first.
+__global__ void k_pack_rows(PairTable t) {
+    const int w = t.ne + 4;
+    const size_t total = (size_t)t.n * t.kmax * w, n = t.n;
+    for (size_t x = blockIdx.x * (size_t)blockDim.x + threadIdx.x; x < total;
+         x += (size_t)gridDim.x * blockDim.x) {
+        const int f = (int)(x % w);
+        const size_t r = x / w;                      // pair * kmax + slot
+        const size_t pr = r / t.kmax, k = r % t.kmax;
+        if (f < 4) {
+            t.rp[r * 4 + f] = f == 0 ? t.p[k * n + pr] : t.P[(k * 3 + f - 1) * n + pr];
+        } else {
+            const double v = t.E[(k * t.ne + f - 4) * n + pr];
+            t.rE[r * t.ne + f - 4] = v;
+            t.rEf[r * t.ne + f - 4] = (float)v;
+        }
+    }
+}
+
+hipError_t launch_pack_rows(const PairTable &t, hipStream_t s) {
+    if (t.n == 0) return hipSuccess;
+    const size_t total = (size_t)t.n * t.kmax * (t.ne + 4);
+    const size_t b = (total + 255) / 256;
+    hipLaunchKernelGGL(k_pack_rows, dim3((unsigned)(b < 16384 ? b : 16384)), dim3(256), 0, s, t);
+    return hipGetLastError();
+}
+
 // Pair order of one class (element (cd, k) at off + cd * n + k): src names
 // each element's place in the packed matrices, pos the inverse.
 __global__ void k_pair_order(PairTable t, int n1, int n2, long long off,
