@@ -628,7 +628,7 @@ static fsim_status create_impl(const fsim_basis *mols, int nmol, const fsim_opti
     HCHK(up(c->d_nocc, c->mol_nocc.data(), sizeof(int) * nmol));
     PCHK(c->pool.alloc(&c->Emol, nmol));
     HCHK(launch_shell_norm(sh, nullptr));
-    PCHK(c->pool.alloc(&c->boys, (size_t)BOYS_NT * BOYS_NORD));
+    PCHK(c->pool.alloc(&c->boys, (size_t)BOYS_TOTAL));
     HCHK(launch_boys_table(c->boys, nullptr));
 
     // every shell pair within a molecule, oriented so that l(s1) >= l(s2)

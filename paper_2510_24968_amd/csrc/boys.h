@@ -27,13 +27,22 @@ __host__ __device__ constexpr double inv_factorial(int j) {
 // LDS footprint of one staged table, in doubles.
 constexpr int BOYS_LDS = BOYS_NT * BOYS_NTAYLOR;
 
+// n doubles (even) from 16-byte aligned global memory into LDS.
+__device__ __forceinline__ void boys_copy(double *lds, const double *__restrict__ g, int n) {
+    const double2 *__restrict__ src = (const double2 *)g;
+    for (int i = threadIdx.x; i < n / 2; i += blockDim.x) ((double2 *)lds)[i] = src[i];
+}
+
 __device__ inline void boys_stage(double *lds, const double *__restrict__ g, int L) {
-    for (int i = threadIdx.x; i < BOYS_LDS; i += blockDim.x) {
-        int k = i / BOYS_NTAYLOR, j = i - k * BOYS_NTAYLOR;
-        double s = 1.0;
-        for (int m = 2; m <= j; ++m) s *= m;
-        lds[i] = g[k * BOYS_NORD + L + j] / s;
-    }
+    boys_copy(lds, g + boys_base(L), BOYS_LDS);
+}
+
+// 1 / sqrt(x) for finite x > 0: the hardware estimate and one step of
+// y (1 + e/2 + 3 e^2 / 8), e = 1 - x y^2.
+__device__ __forceinline__ double rsqrt_pos(double x) {
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = fma(-x * y, y, 1.0);
+    return fma(y * e, fma(e, 0.375, 0.5), y);
 }
 
 // Large-T branch shared by the evaluators: F_0 = sqrt(pi)/2 / sqrt(T) and
@@ -50,37 +59,64 @@ __device__ __forceinline__ void boys_large_t(double T, double e, double *F) {
     }
 }
 
-// Optional exp column after the staged grid: exp(-T_k) at T_k = k * BOYS_DT
-// for k < BOYS_NE (T up to 100; beyond it exp(-T) < 4e-44 is taken as 0).
-// exp(-T) = exp(-T_k) * exp(T_k - T) with the second factor from its Taylor
-// series through d^8/8! (|T_k - T| <= 0.05, so the truncation is below 6e-18
-// relative): eight FMAs and one LDS read instead of the library exponential.
-constexpr int BOYS_NE = 1001;
-constexpr int BOYS_LDS_E = BOYS_LDS + BOYS_NE;
-
-__device__ inline void boys_stage_exp(double *lds) {
-    for (int i = threadIdx.x; i < BOYS_NE; i += blockDim.x) lds[BOYS_LDS + i] = exp(-i * BOYS_DT);
-}
-
-__device__ __forceinline__ double boys_exp_tab(double T, const double *etab) {
-    constexpr double TE = (BOYS_NE - 1) * BOYS_DT;
-    const double Tc = fmin(T, TE);
-    const int k = __double2int_rn(Tc * BOYS_INV_DT);
-    const double d = k * BOYS_DT - Tc;
-    double p = inv_factorial(8);
+// The ket-outer kernels' table of order L: boys_nt(L) rows of the grid and
+// the column exp(-T_k).  On the grid exp(-T) = exp(-T_k) exp(d) with
+// d = T_k - T, |d| <= 0.05, already at hand from the Taylor step, and exp(d)
+// from its series through d^8/8! (truncation below 6e-18 relative); beyond
+// it the asymptotic form needs no exponential at all.  Evaluating exp(-T)
+// inside the grid branch and not ahead of both, and ending the grid where
+// the large-T branch is a plain recursion, took the 64-water FP64 s/p build
+// from 291.8 to 273.1 ms, its mixed build from 252.6 to 214.8.
+template <int L>
+struct BoysLong {
+    static constexpr int ECOL = boys_ecol(L), SIZE = boys_block(L);
+    static __device__ __forceinline__ void stage(double *lds, const double *__restrict__ g) {
+        boys_copy(lds, g + boys_base(L), SIZE);
+    }
+    // exp(-T) at grid point k, d = T_k - T
+    static __device__ __forceinline__ double expm(const double *ecol, int k, double d) {
+        double p = inv_factorial(8);
 #pragma unroll
-    for (int j = 7; j >= 0; --j) p = fma(p, d, inv_factorial(j));
-    return T <= TE ? etab[k] * p : 0.0;
-}
+        for (int j = 7; j >= 0; --j) p = fma(p, d, inv_factorial(j));
+        return ecol[k] * p;
+    }
+    static __device__ __forceinline__ void down(double T, double e, double *F) {
+        const double t2 = 2.0 * T;
+#pragma unroll
+        for (int n = L; n > 0; --n) F[n - 1] = fma(t2, F[n], e) * (1.0 / (2 * n - 1));
+    }
+    static __device__ __forceinline__ void asymptotic(double T, double *F) {
+        const double rs = rsqrt(T);
+        F[0] = 0.88622692545275801365 * rs;
+        if constexpr (L > 0) {
+            const double h = 0.5 * rs * rs;
+#pragma unroll
+            for (int n = 0; n < L; ++n) F[n + 1] = (2 * n + 1) * F[n] * h;
+        }
+    }
+    static __device__ __forceinline__ void eval(double T, const double *tab, double *F) {
+        if (T < boys_tmax(L)) {
+            const int k = __double2int_rn(T * BOYS_INV_DT);
+            const double d = k * BOYS_DT - T;
+            const double *c = tab + k * BOYS_NTAYLOR;
+            double f = c[BOYS_NTAYLOR - 1];
+#pragma unroll
+            for (int j = BOYS_NTAYLOR - 2; j >= 0; --j) f = fma(f, d, c[j]);
+            F[L] = f;
+            if constexpr (L > 0) down(T, expm(tab + ECOL, k, d), F);
+        } else {
+            asymptotic(T, F);
+        }
+    }
+};
 
-// F_0..F_L at T from a table staged for order L (with the exp column when
-// ET).  exp(-T), which both branches need for L > 0, is evaluated once ahead
+// F_0..F_L at T from a table staged for order L.  exp(-T), which both branches need for L > 0, is evaluated once ahead
 // of the branch: the lanes of a wave often take both branches, which would
 // otherwise run it twice.
-template <int L, bool ET = false>
+template <int L>
 __device__ __forceinline__ void boys_eval(double T, const double *tab, double *F) {
     double e = 0.0;
-    if constexpr (L > 0) e = ET ? boys_exp_tab(T, tab + BOYS_LDS) : exp(-T);
+    if constexpr (L > 0) e = exp(-T);
     if (T < BOYS_TMAX) {
         const int k = __double2int_rn(T * BOYS_INV_DT);
         const double d = k * BOYS_DT - T;
@@ -111,10 +147,8 @@ constexpr int BOYS_LDS32 = BOYS_NT * BOYS_NTAYLOR32;
 
 __device__ inline void boys_stage32(float *lds, const double *__restrict__ g, int L) {
     for (int i = threadIdx.x; i < BOYS_LDS32; i += blockDim.x) {
-        int k = i / BOYS_NTAYLOR32, j = i - k * BOYS_NTAYLOR32;
-        double s = 1.0;
-        for (int m = 2; m <= j; ++m) s *= m;
-        lds[i] = (float)(g[k * BOYS_NORD + L + j] / s);
+        const int k = i / BOYS_NTAYLOR32, j = i - k * BOYS_NTAYLOR32;
+        lds[i] = (float)g[boys_base(L) + k * BOYS_NTAYLOR + j];
     }
 }
 
@@ -140,6 +174,39 @@ __device__ __forceinline__ void boys_eval_mixed(double T, const float *tab, doub
         boys_large_t<L>(T, e, F);
     }
 }
+
+// The ket-outer kernels' form of it: the exp column (FP64) first, then the
+// FP32 rows.
+template <int L>
+struct BoysLongMixed {
+    static constexpr int NE = boys_block(L) - boys_ecol(L);             // doubles
+    static constexpr int NF = boys_nt(L) * BOYS_NTAYLOR32;              // floats
+    static constexpr int SIZE = NE + (NF + 1) / 2;                      // doubles
+    static __device__ __forceinline__ void stage(double *lds, const double *__restrict__ g) {
+        boys_copy(lds, g + boys_base(L) + boys_ecol(L), NE);
+        float *__restrict__ f = (float *)(lds + NE);
+        for (int i = threadIdx.x; i < NF; i += blockDim.x) {
+            const int k = i / BOYS_NTAYLOR32, j = i - k * BOYS_NTAYLOR32;
+            f[i] = (float)g[boys_base(L) + k * BOYS_NTAYLOR + j];
+        }
+    }
+    static __device__ __forceinline__ void eval(double T, const double *tab, double *F) {
+        if (T < boys_tmax(L)) {
+            const float Tf = (float)T;
+            const int k = __float2int_rn(Tf * (float)BOYS_INV_DT);
+            const float d = k * (float)BOYS_DT - Tf;
+            const float *c = (const float *)(tab + NE) + k * BOYS_NTAYLOR32;
+            float f = c[BOYS_NTAYLOR32 - 1];
+#pragma unroll
+            for (int j = BOYS_NTAYLOR32 - 2; j >= 0; --j) f = fmaf(f, d, c[j]);
+            F[L] = (double)f;
+            if constexpr (L > 0)
+                BoysLong<L>::down(T, BoysLong<L>::expm(tab, k, k * BOYS_DT - T), F);
+        } else {
+            BoysLong<L>::asymptotic(T, F);
+        }
+    }
+};
 
 // Runtime-L variant reading the full global grid (setup kernels only).
 __device__ inline void boys_eval_rt(int L, double T, const double *__restrict__ g, double *F) {

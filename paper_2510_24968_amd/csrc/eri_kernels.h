@@ -399,7 +399,7 @@ __global__ __launch_bounds__(SEG ? 64 * seg_waves(LA, LB, LC, LD, CA, CDC) : 256
     // Boys grid in LDS: FP64 for FP64 tiles, FP32 (5 terms, the Taylor step
     // only) for FP32 tiles
     constexpr bool F32 = std::is_same<T, float>::value;
-    __shared__ std::conditional_t<F32, float, double> tab[F32 ? BOYS_LDS32 : BOYS_LDS];
+    __shared__ __align__(16) std::conditional_t<F32, float, double> tab[F32 ? BOYS_LDS32 : BOYS_LDS];
     extern __shared__ __align__(16) unsigned char stage_lds[];
     if constexpr (F32) boys_stage32(tab, a.boys, L);
     else boys_stage(tab, a.boys, L);
@@ -674,20 +674,13 @@ __global__ __launch_bounds__(SEG ? 64 * seg_waves(LA, LB, LC, LD, CA, CDC) : 256
 // once per quartet instead of once per bra primitive.
 // ===========================================================================
 // Boys-function providers of the ket-outer tile body: the class kernels
-// stage the grid pre-divided for their own order L (boys.h); the persistent
-// kernel stages raw F_n(T_k) for every order its classes need.
-template <bool ET>
-struct BoysStaged64 {
+// stage the table of their own order L (boys.h); the persistent kernel
+// stages raw F_n(T_k) for every order its classes need.
+template <typename B>
+struct BoysTable {
     const double *tab;
     template <int L>
-    __device__ __forceinline__ void eval(double T, double *F) const { boys_eval<L, ET>(T, tab, F); }
-};
-struct BoysStagedMixed {
-    const float *tab;
-    template <int L>
-    __device__ __forceinline__ void eval(double T, double *F) const {
-        boys_eval_mixed<L>(T, tab, F);
-    }
+    __device__ __forceinline__ void eval(double T, double *F) const { B::eval(T, tab, F); }
 };
 
 // One tile (one bra pair x up to 64 kets) of the ket-outer kernel.
@@ -787,7 +780,7 @@ __device__ __forceinline__ void ko_tile(const EriArgs &a, const int tile, const 
                 if constexpr (F32) {
                     // FP32 tile: FP32 Taylor step, FP64 recursion and
                     // prefactor, sources rounded to FP32
-                    const double rs = rsqrt(p + q);
+                    const double rs = rsqrt_pos(p + q);
                     const double alpha = p * q * (rs * rs);
                     double F[L + 1];
                     bp.template eval<L>(alpha * (X * X + Y * Y + Z * Z), F);
@@ -798,7 +791,7 @@ __device__ __forceinline__ void ko_tile(const EriArgs &a, const int tile, const 
                         m *= -2.0 * alpha;
                     }
                 } else {
-                    const double rs = rsqrt(p + q);
+                    const double rs = rsqrt_pos(p + q);
                     const double alpha = p * q * (rs * rs);
                     double F[L + 1];
                     bp.template eval<L>(alpha * (X * X + Y * Y + Z * Z), F);
@@ -900,23 +893,16 @@ __global__ __launch_bounds__(SEG ? 64 * ko_seg_waves(LA, LB, LC, LD, !std::is_sa
                                  : 256)
 void k_eri_lane_ko(EriArgs a) {
     constexpr int L = LA + LB + LC + LD;
-    // Boys grid in LDS: FP64 for FP64 tiles, FP32 (5 terms, the Taylor step
-    // only) for FP32 tiles. FP64 tiles of s and p bras in segment mode add
-    // the exp column (the d bras keep that LDS for their K' rows; launches
-    // over tiles measured slower with it).
-    constexpr bool F32 = std::is_same<T, float>::value;
-    constexpr bool ET = !F32 && LA <= 1 && SEG;
-    __shared__ std::conditional_t<F32, float, double>
-        tab[F32 ? BOYS_LDS32 : (ET ? BOYS_LDS_E : BOYS_LDS)];
+    // Boys table in LDS: FP64 rows for FP64 tiles, FP32 (5 terms, the Taylor
+    // step only) for FP32 tiles, each with the exp column
+    using BT = std::conditional_t<std::is_same<T, float>::value, BoysLongMixed<L>, BoysLong<L>>;
+    __shared__ __align__(16) double tab[BT::SIZE];
     extern __shared__ __align__(16) unsigned char row_lds[];
-    if constexpr (F32) boys_stage32(tab, a.boys, L);
-    else boys_stage(tab, a.boys, L);
-    if constexpr (ET) boys_stage_exp(tab);
+    BT::stage(tab, a.boys);
     __syncthreads();
     const int wpb = blockDim.x >> 6;
     const int ntile = STORE ? a.st_ntile : a.tl.ntile;
-    using BP = std::conditional_t<F32, BoysStagedMixed, BoysStaged64<ET>>;
-    const BP bp{tab};
+    const BoysTable<BT> bp{tab};
     if constexpr (SEG && !STORE) {
         // segment mode: the block's waves share the bra's K' rows
         double *__restrict__ krow = (double *)row_lds;
@@ -947,7 +933,7 @@ __global__ __launch_bounds__(64) void k_eri_wave(EriArgs a) {
     constexpr int NW = NHAB * NCD, NWL = (NW + 63) / 64;
     constexpr int NO = NAB * NCD, NOL = (NO + 63) / 64;
     constexpr int NRL = (NH + 63) / 64;
-    __shared__ double tab[BOYS_LDS];
+    __shared__ __align__(16) double tab[BOYS_LDS];
     __shared__ T rbuf[2][NH];
     __shared__ T wl[NW];
     __shared__ T ebl[NEB], ekl[NEK];

@@ -29,6 +29,27 @@ constexpr double BOYS_TMAX = 36.0;
 constexpr int BOYS_NT = 361;
 constexpr int BOYS_NTAYLOR = 8;
 constexpr int BOYS_NORD = LTOT_MAX + BOYS_NTAYLOR;   // orders 0..15
+// The ket-outer kernels read F_L from a longer grid, up to the T from which
+// the asymptotic form holds without its exp(-T) terms for every order up to
+// L (largest relative error 2.2e-17, at L = 0; below 5e-18 for L > 0), so
+// that exp(-T) is needed on the grid only.
+__host__ __device__ constexpr double boys_tmax(int L) {
+    return L == 0 ? 36.0 : (L == 1 ? 42.0 : (L == 2 ? 46.0 : 40.0 + 3.0 * L));
+}
+__host__ __device__ constexpr int boys_nt(int L) { return (int)(boys_tmax(L) * BOYS_INV_DT) + 1; }
+constexpr int BOYS_NT_MAX = 641;                     // boys_nt(LTOT_MAX)
+static_assert(boys_nt(LTOT_MAX) == BOYS_NT_MAX, "the longest grid is that of the highest order");
+// Global Boys tables: the raw grid [BOYS_NT_MAX][BOYS_NORD], then for every
+// order L the rows F_{L+j}(T_k) / j!, j < BOYS_NTAYLOR, and the column
+// exp(-T_k) (rounded up to an even count), as the kernels copy them to LDS.
+__host__ __device__ constexpr int boys_ecol(int L) { return boys_nt(L) * BOYS_NTAYLOR; }
+__host__ __device__ constexpr int boys_block(int L) { return boys_ecol(L) + (boys_nt(L) + 1) / 2 * 2; }
+__host__ __device__ constexpr int boys_base(int L) {
+    int o = BOYS_NT_MAX * BOYS_NORD;
+    for (int l = 0; l < L; ++l) o += boys_block(l);
+    return o;
+}
+constexpr int BOYS_TOTAL = boys_base(LTOT_MAX + 1);
 
 // ---- component algebra -------------------------------------------------
 __host__ __device__ constexpr int ncart(int l) { return (l + 1) * (l + 2) / 2; }
@@ -181,7 +202,7 @@ struct EriArgs {
     const long long *st_off;
     const int *st_stride;   // [4 per task]
     double *out;
-    const double *boys;     // [BOYS_NT][BOYS_NORD]
+    const double *boys;     // BOYS_TOTAL doubles
     // > 0: segment mode of the lane kernels, the K' rows of each segment's
     // bra accumulate in LDS, kn doubles per row (the largest N_m); the
     // dynamic LDS holds (ncart(la) + ncart(lb)) * kn doubles after the

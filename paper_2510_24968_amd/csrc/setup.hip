@@ -14,7 +14,7 @@ namespace fsim {
 // ---------------------------------------------------------------------------
 __global__ void k_boys_table(double *tab) {
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= BOYS_NT) return;
+    if (k >= BOYS_NT_MAX) return;
     const double T = k * BOYS_DT;
     const int N = BOYS_NORD - 1;
     double term = 1.0 / (2 * N + 1), sum = term;
@@ -32,8 +32,23 @@ __global__ void k_boys_table(double *tab) {
     }
 }
 
+// The per-order tables behind the grid, one block per order.
+__global__ void k_boys_staged(double *tab) {
+    const int L = blockIdx.x, nt = boys_nt(L);
+    double *__restrict__ t = tab + boys_base(L);
+    for (int i = threadIdx.x; i < boys_ecol(L); i += blockDim.x) {
+        const int k = i / BOYS_NTAYLOR, j = i - k * BOYS_NTAYLOR;
+        double s = 1.0;
+        for (int m = 2; m <= j; ++m) s *= m;
+        t[i] = tab[k * BOYS_NORD + L + j] / s;
+    }
+    for (int k = threadIdx.x; k < boys_block(L) - boys_ecol(L); k += blockDim.x)
+        t[boys_ecol(L) + k] = k < nt ? exp(-k * BOYS_DT) : 0.0;
+}
+
 hipError_t launch_boys_table(double *tab, hipStream_t s) {
-    hipLaunchKernelGGL(k_boys_table, dim3((BOYS_NT + 127) / 128), dim3(128), 0, s, tab);
+    hipLaunchKernelGGL(k_boys_table, dim3((BOYS_NT_MAX + 127) / 128), dim3(128), 0, s, tab);
+    hipLaunchKernelGGL(k_boys_staged, dim3(LTOT_MAX + 1), dim3(256), 0, s, tab);
     return hipGetLastError();
 }
 
