@@ -287,6 +287,12 @@ static fsim_status alloc_table(DevPool &pool, PairTable &t, int l1, int l2, int 
     HIPCHK(pool.alloc(&t.rp, (size_t)kmax * 4 * n));
     HIPCHK(pool.alloc(&t.rE, (size_t)kmax * t.ne * n));
     HIPCHK(pool.alloc(&t.rEf, (size_t)kmax * t.ne * n));
+    if (pclass(l1, l2) <= KO_PCLASS_MAX) {
+        const size_t ns = (size_t)kmax * n_scaled(l1, l2) * n;
+        HIPCHK(pool.alloc(&t.S0, (size_t)kmax * n));
+        HIPCHK(pool.alloc(&t.S, ns));
+        HIPCHK(pool.alloc(&t.Sf, ns));
+    }
     return FSIM_OK;
 }
 

@@ -116,6 +116,25 @@ __host__ __device__ constexpr int n_entries(int l1, int l2) {
     return box_off(l1, l2, ncart(l1) * ncart(l2));
 }
 
+// 1 / sqrt((2lx-1)!! (2ly-1)!! (2lz-1)!!) for component c of shell l.
+__host__ __device__ constexpr double comp_norm(int l, int c) {
+    double d = 1.0;
+    for (int dir = 0; dir < 3; ++dir)
+        for (int k = 2 * cart_exp(l, c, dir) - 1; k > 1; k -= 2) d *= k;
+    return d == 1.0 ? 1.0 : (d == 3.0 ? 0.57735026918962576451 : 1.0 / __builtin_sqrt(d));
+}
+
+// Scaled ket entries: the last entry of every component pair's box is the
+// same product K (1/2q)^(l1+l2) up to the components' norms, so the other
+// entries divided by it leave one factor per primitive pair.  Offset of
+// component pair cp in that list (its last entry, 1, is not stored).
+__host__ __device__ constexpr int scaled_off(int l1, int l2, int cp) {
+    return box_off(l1, l2, cp) - cp;
+}
+__host__ __device__ constexpr int n_scaled(int l1, int l2) {
+    return scaled_off(l1, l2, ncart(l1) * ncart(l2));
+}
+
 __host__ __device__ constexpr int pclass(int l1, int l2) {   // l1 >= l2
     return l1 * (l1 + 1) / 2 + l2;
 }
@@ -151,7 +170,17 @@ struct PairTable {
     double *rp = nullptr;                 // [n][kmax][4]: p, P
     double *rE = nullptr;                 // [n][kmax][ne]
     float *rEf = nullptr;                 // FP32 copy of rE
+    // scaled entries (ss, ps, pp and ds pairs, the kets of the ket-outer
+    // kernels): the common factor, and every box entry but each box's last
+    // divided by that last one (n_scaled per primitive pair)
+    double *S0 = nullptr;                 // [kmax][n]
+    double *S = nullptr;                  // [kmax][n_scaled][n]
+    float *Sf = nullptr;                  // FP32 copy of S
 };
+
+// Pair classes that serve as bras, and so also as kets, of the ket-outer
+// kernels.
+constexpr int KO_PCLASS_MAX = 3;
 
 // Tile lists of one quartet class and precision: bra pair b owns the ket
 // range [ket_lo[b], ket_hi[b]) cut into tiles of TILE kets.
@@ -235,7 +264,8 @@ hipError_t launch_build_pairs(const ShellsDev &sh, PairTable &t, const int *pair
 // packed matrix element of component pair cd of pair k, pos the inverse.
 hipError_t launch_pair_order(const PairTable &t, long long off, const long long *mol_off,
                              const int *mol_n, int *src, int *pos, hipStream_t s);
-// Fill the row copies rp, rE, rEf from the columns (setup.hip).
+// Fill the row copies rp, rE, rEf and the scaled entries S0, S, Sf from the
+// columns (setup.hip).
 hipError_t launch_pack_rows(const PairTable &t, hipStream_t s);
 // Drop the primitive pairs of every pair whose Schwarz bound times
 // qmax_mol[mol] is below tau_prim, compacting the slots in place (setup.hip).

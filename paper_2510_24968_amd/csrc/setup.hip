@@ -83,14 +83,6 @@ hipError_t launch_shell_norm(const ShellsDev &sh, hipStream_t s) {
     return hipGetLastError();
 }
 
-// 1 / sqrt((2lx-1)!! (2ly-1)!! (2lz-1)!!) for component c of shell l.
-__host__ __device__ constexpr double comp_norm(int l, int c) {
-    double d = 1.0;
-    for (int dir = 0; dir < 3; ++dir)
-        for (int k = 2 * cart_exp(l, c, dir) - 1; k > 1; k -= 2) d *= k;
-    return d == 1.0 ? 1.0 : (d == 3.0 ? 0.57735026918962576451 : 1.0 / __builtin_sqrt(d));
-}
-
 // One-direction Hermite coefficients E^{ij}_t, i <= IM, j <= JM (Sec. 2.1.3:
 // E^{00}_0 = exp(-mu X_AB^2); recurrence-A raises i with X_PA, recurrence-B
 // raises j with X_PB; zero outside 0 <= t <= i + j).
@@ -212,11 +204,46 @@ __global__ void k_pack_rows(PairTable t) {
     }
 }
 
+// Scaled entries, one thread per (pair, slot).  The factor is taken from a
+// component pair of unit norms (the last of an s or p pair, xy of a ds pair).
+// A factor that has underflowed leaves the slot empty: every entry is then
+// far below the smallest number an integral could show.
+template <int L1, int L2>
+__global__ void k_scale_entries(PairTable t) {
+    constexpr int NCP = ncart(L1) * ncart(L2), NE = n_entries(L1, L2), NS = n_scaled(L1, L2);
+    constexpr int REF = L1 == 2 ? ncart(L2) : NCP - 1;
+    static_assert(comp_norm(L1, REF / ncart(L2)) == 1.0 && comp_norm(L2, REF % ncart(L2)) == 1.0,
+                  "the reference component pair has unit norms");
+    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
+    if (idx >= t.n * t.kmax) return;
+    const size_t n = t.n, pr = idx % t.n, k = idx / t.n;
+    auto entry = [&](int e) { return t.E[(k * NE + e) * n + pr]; };
+    t.S0[k * n + pr] = entry(box_off(L1, L2, REF + 1) - 1);
+#pragma unroll
+    for (int cp = 0; cp < NCP; ++cp) {
+        const double last = entry(box_off(L1, L2, cp + 1) - 1);
+        for (int x = 0; x < box_size(L1, L2, cp) - 1; ++x) {
+            const double v = last != 0.0 ? entry(box_off(L1, L2, cp) + x) / last : 0.0;
+            const size_t o = (k * NS + scaled_off(L1, L2, cp) + x) * n + pr;
+            t.S[o] = v;
+            t.Sf[o] = (float)v;
+        }
+    }
+}
+
 hipError_t launch_pack_rows(const PairTable &t, hipStream_t s) {
     if (t.n == 0) return hipSuccess;
     const size_t total = (size_t)t.n * t.kmax * (t.ne + 4);
     const size_t b = (total + 255) / 256;
     hipLaunchKernelGGL(k_pack_rows, dim3((unsigned)(b < 16384 ? b : 16384)), dim3(256), 0, s, t);
+    const dim3 g((t.n * t.kmax + 127) / 128);
+    switch (pclass(t.l1, t.l2)) {
+        case 0: hipLaunchKernelGGL((k_scale_entries<0, 0>), g, dim3(128), 0, s, t); break;
+        case 1: hipLaunchKernelGGL((k_scale_entries<1, 0>), g, dim3(128), 0, s, t); break;
+        case 2: hipLaunchKernelGGL((k_scale_entries<1, 1>), g, dim3(128), 0, s, t); break;
+        case 3: hipLaunchKernelGGL((k_scale_entries<2, 0>), g, dim3(128), 0, s, t); break;
+        default: break;
+    }
     return hipGetLastError();
 }
 
