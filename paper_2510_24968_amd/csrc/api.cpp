@@ -2085,6 +2085,10 @@ static bool wide_distinct(int X, int Y) {
     return !f160 || (f192 && n192 < n160);
 }
 
+// Classes the ket-outer kernel serves: ss, ps, pp and ds bras, dp bras with
+// ss and ps kets.
+static bool ko_candidate(int X, int Y) { return X <= KO_PCLASS_MAX || (X == 4 && Y <= 1); }
+
 extern "C" fsim_status fsim_autotune(fsim_ctx *c, const double *D, fsim_precision prec,
                                      void *stream) {
     if (!c || !D) return fail(FSIM_EINVAL, "NULL argument");
@@ -2118,8 +2122,8 @@ extern "C" fsim_status fsim_autotune(fsim_ctx *c, const double *D, fsim_precisio
                 continue;   // one wave per block, or segment mode
             if (w == 3 && !c->krow_lds) continue;
             // the wave kernel is only a candidate for the high angular-momentum
-            // classes (L >= 5), the ket-outer kernel only for the ss, ps, pp
-            // and ds bras, and variant 5 only where it is a kernel of its own;
+            // classes (L >= 5), the ket-outer kernel only for those it serves,
+            // and variant 5 only where it is a kernel of its own;
             // elsewhere those classes keep a lane variant during that pass and
             // are not scored in it
             const bool wave = v == ERI_VARIANT_WAVE, ko = v == ERI_VARIANT_KO,
@@ -2130,7 +2134,7 @@ extern "C" fsim_status fsim_autotune(fsim_ctx *c, const double *D, fsim_precisio
             for (int X = 0; X < NPCLASS; ++X)
                 for (int Y = 0; Y < NPCLASS; ++Y)
                     for (int f = 0; f < 2; ++f) {
-                        const bool cand = (!wave || Ltot(X, Y) >= 5) && (!ko || X <= 3) &&
+                        const bool cand = (!wave || Ltot(X, Y) >= 5) && (!ko || ko_candidate(X, Y)) &&
                                           (!wide || wide_distinct(X, Y)) && (!mf || X >= 3);
                         c->variant[X][Y][f] = cand ? v : ERI_DEFAULT_VARIANT;
                         c->wpb[X][Y][f] = wpbs[w];
@@ -2146,7 +2150,7 @@ extern "C" fsim_status fsim_autotune(fsim_ctx *c, const double *D, fsim_precisio
             }
             for (const auto &r : c->prof)
                 if ((!wave || Ltot(r.bra_class, r.ket_class) >= 5) &&
-                    (!ko || r.bra_class <= 3) &&
+                    (!ko || ko_candidate(r.bra_class, r.ket_class)) &&
                     (!wide || wide_distinct(r.bra_class, r.ket_class)) &&
                     (!mf || r.bra_class >= 3) &&
                     r.ms < best[r.bra_class][r.ket_class][r.fp32]) {

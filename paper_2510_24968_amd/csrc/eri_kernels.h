@@ -381,12 +381,14 @@ __device__ __forceinline__ void run_segments(const EriArgs &a, double *__restric
     }
 }
 
-// Minimum waves per SIMD the lane kernel is compiled for.  d bras with a
-// live set of up to 128 FP64 values are held to two resident waves (256
-// registers each); every other kernel is left to the compiler, which
-// measured faster for the s and p bras.
+// Minimum waves per SIMD the lane kernel is compiled for.  ds and dp bras
+// with a live set of up to 128 FP64 values are held to two resident waves
+// (256 registers each); every other kernel is left to the compiler, which
+// measured faster for the s and p bras, and for the dd bras, whose staged
+// ket entries spilled to scratch at two ((dd|ps) FP64, 64 waters: 13.9 ms
+// with 340 bytes of scratch per lane, 5.1 ms without).
 __host__ __device__ constexpr int lane_min_waves(int la, int lb, int lc, int ld, int ca, int cdc) {
-    return la == 2 && lane_live(la, lb, lc, ld, ca, cdc) <= 128 ? 2 : 1;
+    return la == 2 && lb < 2 && lane_live(la, lb, lc, ld, ca, cdc) <= 128 ? 2 : 1;
 }
 
 // Blocks of the lane kernel in segment mode: 8 waves where the kernel is held
@@ -427,13 +429,10 @@ __global__ __launch_bounds__(SEG ? 64 * seg_waves(LA, LB, LC, LD, CA, CDC) : 256
     double *__restrict__ sp = (double *)(stage_lds + (size_t)(threadIdx.x >> 6) * a.stage_bytes);
     T *__restrict__ se = (T *)(sp + 4 * ks);
     auto stage = [&](int bra_, int i0, int cnt) {
-        for (int x = lane; x < cnt * 4; x += 64) {
-            const int s = x >> 2, f = x & 3;
-            sp[x] = f == 0 ? a.bra.p[(size_t)(i0 + s) * nb + bra_]
-                           : a.bra.P[((size_t)(i0 + s) * 3 + f - 1) * nb + bra_];
-        }
-        for (int x = lane; x < cnt * NEB; x += 64)
-            se[x] = Eb[((size_t)i0 * NEB + x) * nb + bra_];
+        // from the row copies, which a wave reads in whole cache lines
+        const size_t r0 = (size_t)bra_ * a.bra.kmax + i0;
+        for (int x = lane; x < cnt * 4; x += 64) sp[x] = a.bra.rp[r0 * 4 + x];
+        for (int x = lane; x < cnt * NEB; x += 64) se[x] = rtab<T>(a.bra)[r0 * NEB + x];
         // the wave's own LDS writes complete before its reads
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -814,18 +813,19 @@ __device__ __forceinline__ void ko_tile(const EriArgs &a, const int tile, const 
                 }
                 T r[NH];
                 hermite_r<L, T>(src, T(X), T(Y), T(Z), r);
-                // ket step for this primitive quartet
-                T V[NCDc][NHAB];
+                // one ket component at a time: its ket step, then its bra step
+                const ConstPtr<T> eb = re + i * NEB;
                 static_for<NCDc>([&](auto cdl_) {
                     constexpr int cdl = decltype(cdl_)::value;
                     constexpr int cd = CD0 + cdl;
                     constexpr int bx = box_dim(LC, LD, cd, 0), by = box_dim(LC, LD, cd, 1),
                                   bz = box_dim(LC, LD, cd, 2);
                     constexpr int eo = scaled_off(LC, LD, cd);
+                    T V[NHAB];
                     static_for<NHAB>([&](auto h_) {
                         constexpr int h = decltype(h_)::value;
                         const T rt = r[hidx(hidx_t(h) + bx, hidx_u(h) + by, hidx_v(h) + bz)];
-                        V[cdl][h] = ((bx + by + bz) & 1) ? -rt : rt;
+                        V[h] = ((bx + by + bz) & 1) ? -rt : rt;
                     });
                     static_for<bx + 1>([&](auto ta_) {
                         constexpr int ta = decltype(ta_)::value;
@@ -841,32 +841,26 @@ __device__ __forceinline__ void ko_tile(const EriArgs &a, const int tile, const 
                                         constexpr int h = decltype(h_)::value;
                                         constexpr int ri = hidx(hidx_t(h) + ta, hidx_u(h) + nu,
                                                                 hidx_v(h) + ph);
-                                        V[cdl][h] = fma(ev, r[ri], V[cdl][h]);
+                                        V[h] = fma(ev, r[ri], V[h]);
                                     });
                                 }
                             });
                         });
                     });
-                });
-                // bra step for this primitive quartet
-                const ConstPtr<T> eb = re + i * NEB;
-                static_for<NABc>([&](auto abl_) {
-                    constexpr int abl = decltype(abl_)::value;
-                    constexpr int ab = (A0 + abl / NB) * NB + abl % NB;
-                    constexpr int ax = box_dim(LA, LB, ab, 0), ay = box_dim(LA, LB, ab, 1),
-                                  az = box_dim(LA, LB, ab, 2);
-                    constexpr int ao = box_off(LA, LB, ab);
-                    static_for<ax + 1>([&](auto t_) {
-                        constexpr int t = decltype(t_)::value;
-                        static_for<ay + 1>([&](auto u_) {
-                            constexpr int u = decltype(u_)::value;
-                            static_for<az + 1>([&](auto v_) {
-                                constexpr int v = decltype(v_)::value;
-                                constexpr int e = ao + (t * (ay + 1) + u) * (az + 1) + v;
-                                const T ebv = eb[e];
-                                static_for<NCDc>([&](auto cdl_) {
-                                    constexpr int cdl = decltype(cdl_)::value;
-                                    out[abl][cdl] = fma(ebv, V[cdl][hidx(t, u, v)], out[abl][cdl]);
+                    static_for<NABc>([&](auto abl_) {
+                        constexpr int abl = decltype(abl_)::value;
+                        constexpr int ab = (A0 + abl / NB) * NB + abl % NB;
+                        constexpr int ax = box_dim(LA, LB, ab, 0), ay = box_dim(LA, LB, ab, 1),
+                                      az = box_dim(LA, LB, ab, 2);
+                        constexpr int ao = box_off(LA, LB, ab);
+                        static_for<ax + 1>([&](auto t_) {
+                            constexpr int t = decltype(t_)::value;
+                            static_for<ay + 1>([&](auto u_) {
+                                constexpr int u = decltype(u_)::value;
+                                static_for<az + 1>([&](auto v_) {
+                                    constexpr int v = decltype(v_)::value;
+                                    constexpr int e = ao + (t * (ay + 1) + u) * (az + 1) + v;
+                                    out[abl][cdl] = fma(eb[e], V[hidx(t, u, v)], out[abl][cdl]);
                                 });
                             });
                         });
@@ -903,14 +897,47 @@ __device__ __forceinline__ void ko_tile(const EriArgs &a, const int tile, const 
     });
 }
 
-// Blocks of the ket-outer kernel in segment mode: 12 waves for the s/p
-// classes of total angular momentum 2, whose ~150 registers allow three
-// waves per SIMD; 4 (one per SIMD, AGPRs available) for FP64 (ds|pp),
-// which at two waves per SIMD spills to scratch; 8 (two per SIMD)
-// otherwise.
+// Chunks of the ket-outer kernel: block, R^0 and one ket component's V are
+// live at a time; KO_LIVE values leave two waves per SIMD without spills
+// ((pp|pp) in two chunks instead of three, (ds|ds) in one instead of two).
+constexpr int KO_LIVE = 96;
+// The bra classes it serves: ss, ps, pp, ds, and dp for s and ps kets, where
+// the whole block and R^0 fit at once.  Their bra step of 108 entries runs
+// per primitive quartet, where the bra-outer kernel runs it per bra
+// primitive, but that one needs 300 to 400 registers per lane there and
+// spends as many instructions moving them.
+__host__ __device__ constexpr bool ko_serves(int la, int lb, int lc, int ld) {
+    return pclass(la, lb) <= KO_PCLASS_MAX || (la == 2 && lb == 1 && pclass(lc, ld) <= 1);
+}
+__host__ __device__ constexpr int ko_chunk(int la, int lb, int lc, int ld, bool want_a) {
+    int ca = ncart(la), cdc = ncart(lc) * ncart(ld);
+    const int rest = nherm(la + lb) + nherm(la + lb + lc + ld);
+    while (pclass(la, lb) <= KO_PCLASS_MAX && ca * ncart(lb) * cdc + rest > KO_LIVE) {
+        if (cdc > 1) cdc = (cdc + 1) / 2;
+        else if (ca > 1) ca = (ca + 1) / 2;
+        else break;
+    }
+    return want_a ? ca : cdc;
+}
+__host__ __device__ constexpr int ko_ca(int la, int lb, int lc, int ld) {
+    return ko_chunk(la, lb, lc, ld, true);
+}
+__host__ __device__ constexpr int ko_cdc(int la, int lb, int lc, int ld) {
+    return ko_chunk(la, lb, lc, ld, false);
+}
+
+// Blocks of the ket-outer kernel in segment mode.  One block's K' rows fill
+// most of a CU's LDS for large molecules, so the block has as many waves as
+// the registers allow: a live set of up to 30 values runs in 128 registers
+// (16 waves, four per SIMD), up to 60 in 168 (12, three per SIMD), the rest
+// in 256 (8).  The classes of total angular momentum 0 and 1 have few enough
+// rows for two blocks of 8.
 __host__ __device__ constexpr int ko_seg_waves(int la, int lb, int lc, int ld, bool f64) {
-    return la <= 1 && (la + lb + lc + ld == 2 || (f64 && la + lb + lc + ld == 3)) ? 12
-                                             : (f64 && la == 2 && lc == 1 && ld == 1 ? 4 : 8);
+    const int L = la + lb + lc + ld;
+    const int live = ko_ca(la, lb, lc, ld) * ncart(lb) * ko_cdc(la, lb, lc, ld) + nherm(la + lb) +
+                     nherm(L);
+    if (L <= 1) return 8;
+    return live <= (f64 ? 30 : 60) ? 16 : (live <= (f64 ? 60 : 90) ? 12 : 8);
 }
 
 template <int LA, int LB, int LC, int LD, typename T, bool STORE, int CA, int CDC, bool SEG>
@@ -1604,13 +1631,6 @@ constexpr int MAX_CHUNKS = 24;
 
 // LDS per wave for the staged bra primitives of the bra-outer lane kernel
 constexpr int STAGE_BYTES = 3072;
-// the ket-outer kernel serves bra classes with small Hermite boxes (ss, ps,
-// pp, ds: 1, 6, 33, 21 entries), whose per-quartet bra step is cheap
-constexpr int KO_MAX_BRA_BOX = 33;
-static_assert(n_entries(2, 0) <= KO_MAX_BRA_BOX && n_entries(2, 1) > KO_MAX_BRA_BOX &&
-                  pclass(2, 0) == KO_PCLASS_MAX,
-              "the ket-outer bras are the classes up to KO_PCLASS_MAX");
-
 template <int LA, int LB, int LC, int LD, int BUDGET>
 __host__ __device__ constexpr bool lane_fits() {
     return BUDGET > 0 &&
@@ -1693,9 +1713,8 @@ void launch_budget(int ntile, int wpb, const EriArgs &a, hipStream_t s) {
 
 template <int LA, int LB, int LC, int LD, typename T, bool STORE>
 void launch_ko(int ntile, int wpb, const EriArgs &a, hipStream_t s) {
-    constexpr int BUDGET = variant_budget(DEFAULT_VARIANT);
-    if constexpr (n_entries(LA, LB) <= KO_MAX_BRA_BOX && lane_fits<LA, LB, LC, LD, BUDGET>()) {
-        constexpr int CA = chunk_a(LA, LB, LC, LD, BUDGET), CDC = chunk_cd(LA, LB, LC, LD, BUDGET);
+    if constexpr (ko_serves(LA, LB, LC, LD)) {
+        constexpr int CA = ko_ca(LA, LB, LC, LD), CDC = ko_cdc(LA, LB, LC, LD);
         EriArgs b = a;
         b.stage_prims = b.stage_bytes = 0;
         if constexpr (!STORE) {
@@ -1717,7 +1736,7 @@ void launch_ko(int ntile, int wpb, const EriArgs &a, hipStream_t s) {
         hipLaunchKernelGGL((k_eri_lane_ko<LA, LB, LC, LD, T, STORE, CA, CDC, false>), dim3(blocks),
                            dim3(64 * w), 0, s, b);
     } else {
-        launch_budget<LA, LB, LC, LD, T, STORE, BUDGET>(ntile, wpb, a, s);
+        launch_budget<LA, LB, LC, LD, T, STORE, variant_budget(DEFAULT_VARIANT)>(ntile, wpb, a, s);
     }
 }
 

@@ -283,7 +283,6 @@ hipError_t launch_eri_unit(bool store, int variant, int wpb, const EriArgs &a, h
 // first queue position of slot k, start[6] the total.  *counter must be 0
 // at launch.
 constexpr int PERSIST_SLOTS = 6;
-constexpr int PERSIST_BUDGET = 128;   // lane-kernel live-value budget of the tile bodies
 struct PersistArgs {
     EriArgs cls[PERSIST_SLOTS];
     int start[PERSIST_SLOTS + 1];

@@ -80,8 +80,7 @@ template <int SLOT, typename T, typename BP>
 __device__ __forceinline__ void persist_tile(const PersistArgs &p, int tile, const BP &bp) {
     constexpr int X = persist_bra(SLOT), Y = persist_ket(SLOT);
     constexpr int LA = pc_l1(X), LB = pc_l2(X), LC = pc_l1(Y), LD = pc_l2(Y);
-    constexpr int B = PERSIST_BUDGET;
-    ko_tile<LA, LB, LC, LD, T, false, chunk_a(LA, LB, LC, LD, B), chunk_cd(LA, LB, LC, LD, B)>(
+    ko_tile<LA, LB, LC, LD, T, false, ko_ca(LA, LB, LC, LD), ko_cdc(LA, LB, LC, LD)>(
         p.cls[SLOT], tile, bp);
 }
 
@@ -92,12 +91,11 @@ __device__ __forceinline__ void persist_segment(const PersistArgs &p, int sg, co
                                                 double *krow) {
     constexpr int X = persist_bra(SLOT), Y = persist_ket(SLOT);
     constexpr int LA = pc_l1(X), LB = pc_l2(X), LC = pc_l1(Y), LD = pc_l2(Y);
-    constexpr int B = PERSIST_BUDGET;
     const EriArgs &a = p.cls[SLOT];
     const int wave = threadIdx.x >> 6, wpb = blockDim.x >> 6;
     const int t0 = a.tl.seg_t0[sg], nt = a.tl.seg_nt[sg];
     for (int t = t0 + wave; t < t0 + nt; t += wpb)
-        ko_tile<LA, LB, LC, LD, T, false, chunk_a(LA, LB, LC, LD, B), chunk_cd(LA, LB, LC, LD, B)>(
+        ko_tile<LA, LB, LC, LD, T, false, ko_ca(LA, LB, LC, LD), ko_cdc(LA, LB, LC, LD)>(
             a, __builtin_amdgcn_readfirstlane(t), bp, krow, true);
     __syncthreads();
     const long long xoff = a.xcd_stride ? xcd_index() * a.xcd_stride : 0;
