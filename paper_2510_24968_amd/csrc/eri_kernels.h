@@ -1302,6 +1302,59 @@ __device__ __forceinline__ void boys_eval_global(double T, const double *__restr
     }
 }
 
+// Index maps of kernel C, evaluated at compile time: building them in every
+// block cost a lone (dd|dd) quartet 0.61 ms (now 0.04).
+template <int LA, int LB, int LC, int LD>
+struct MfmaMaps {
+    static constexpr int NHAB = nherm(LA + LB), NHCD = nherm(LC + LD);
+    static constexpr int NH = nherm(LA + LB + LC + LD);
+    static constexpr int NAB = ncart(LA) * ncart(LB), NCD = ncart(LC) * ncart(LD);
+    static constexpr int MR1 = (NHAB + 15) / 16 * 16, KR = (NHCD + 3) / 4 * 4;
+    static constexpr int NC16 = (NCD + 15) / 16 * 16;
+    static constexpr int MR2 = (NAB + 15) / 16 * 16, KR2 = (NHAB + 3) / 4 * 4;
+    short rmap[MR1 * KR] = {};     // R^0 index of (h_ab, h_cd), -1 in the padding
+    short kmap[KR * NC16] = {};    // +-(ket entry + 1) with the Hermite sign, 0 outside
+    short bmap[MR2 * KR2] = {};    // bra entry + 1, 0 outside
+    int tuv[NH] = {};              // t | u << 8 | v << 16
+
+    constexpr MfmaMaps() {
+        constexpr int L = LA + LB + LC + LD;
+        for (int t = 0; t <= L; ++t)
+            for (int u = 0; u <= L - t; ++u)
+                for (int v = 0; v <= L - t - u; ++v) tuv[hidx(t, u, v)] = t | u << 8 | v << 16;
+        for (int r = 0; r < MR1; ++r)
+            for (int k = 0; k < KR; ++k) {
+                int id = -1;
+                if (r < NHAB && k < NHCD) {
+                    const int s = tuv[r] + tuv[k];   // the sums stay below 256
+                    id = hidx(s & 255, (s >> 8) & 255, s >> 16);
+                }
+                rmap[r * KR + k] = (short)id;
+            }
+        int o = 0;
+        for (int n = 0; n < NCD; ++n) {
+            const int bx = box_dim(LC, LD, n, 0), by = box_dim(LC, LD, n, 1),
+                      bz = box_dim(LC, LD, n, 2);
+            for (int t = 0; t <= bx; ++t)
+                for (int u = 0; u <= by; ++u)
+                    for (int v = 0; v <= bz; ++v) {
+                        ++o;
+                        kmap[hidx(t, u, v) * NC16 + n] = (short)(((t + u + v) & 1) ? -o : o);
+                    }
+        }
+        o = 0;
+        for (int m = 0; m < NAB; ++m) {
+            const int bx = box_dim(LA, LB, m, 0), by = box_dim(LA, LB, m, 1),
+                      bz = box_dim(LA, LB, m, 2);
+            for (int t = 0; t <= bx; ++t)
+                for (int u = 0; u <= by; ++u)
+                    for (int v = 0; v <= bz; ++v) bmap[m * KR2 + hidx(t, u, v)] = (short)++o;
+        }
+    }
+};
+template <int LA, int LB, int LC, int LD>
+__device__ const MfmaMaps<LA, LB, LC, LD> mfma_maps{};
+
 template <int LA, int LB, int LC, int LD, typename T, bool STORE>
 __global__ __launch_bounds__(64) void k_eri_mfma(EriArgs a) {
     constexpr int L = LA + LB + LC + LD, LAB = LA + LB, LCD = LC + LD;
@@ -1333,47 +1386,18 @@ __global__ __launch_bounds__(64) void k_eri_mfma(EriArgs a) {
     T *wst = (T *)ubuf;
     const int lane = threadIdx.x;
 
-    for (int x = lane; x < KR * NC16; x += 64) {
-        const int k = x / NC16, n = x % NC16;
-        int val = 0;
-        if (k < NHCD && n < NCD) {
-            const int t = hidx_t(k), u = hidx_u(k), v = hidx_v(k);
-            const int bx = box_dim(LC, LD, n, 0), by = box_dim(LC, LD, n, 1),
-                      bz = box_dim(LC, LD, n, 2);
-            if (t <= bx && u <= by && v <= bz) {
-                const int e = box_off(LC, LD, n) + (t * (by + 1) + u) * (bz + 1) + v;
-                val = ((t + u + v) & 1) ? -(e + 1) : e + 1;
-            }
-        }
-        kmap[k][n] = (short)val;
-    }
-    for (int x = lane; x < MR2 * KR2; x += 64) {
-        const int m = x / KR2, k = x % KR2;
-        int val = 0;
-        if (m < NAB && k < NHAB) {
-            const int t = hidx_t(k), u = hidx_u(k), v = hidx_v(k);
-            const int bx = box_dim(LA, LB, m, 0), by = box_dim(LA, LB, m, 1),
-                      bz = box_dim(LA, LB, m, 2);
-            if (t <= bx && u <= by && v <= bz)
-                val = box_off(LA, LB, m) + (t * (by + 1) + u) * (bz + 1) + v + 1;
-        }
-        bmap[m][k] = (short)val;
-    }
-    for (int x = lane; x < MR1 * KR; x += 64) {
-        const int r = x / KR, k = x % KR;
-        rmap[r][k] = (short)((r < NHAB && k < NHCD)
-                                 ? hidx(hidx_t(r) + hidx_t(k), hidx_u(r) + hidx_u(k),
-                                        hidx_v(r) + hidx_v(k))
-                                 : -1);
-    }
+    const MfmaMaps<LA, LB, LC, LD> &maps = mfma_maps<LA, LB, LC, LD>;
+    for (int x = lane; x < KR * NC16; x += 64) (&kmap[0][0])[x] = maps.kmap[x];
+    for (int x = lane; x < MR2 * KR2; x += 64) (&bmap[0][0])[x] = maps.bmap[x];
+    for (int x = lane; x < MR1 * KR; x += 64) (&rmap[0][0])[x] = maps.rmap[x];
     // level decode of the R recursion (as kernel B)
     int rt[NRL], ru[NRL], rv[NRL];
 #pragma unroll
     for (int k = 0; k < NRL; ++k) {
-        const int id = lane + 64 * k < NH ? lane + 64 * k : 0;
-        rt[k] = hidx_t(id);
-        ru[k] = hidx_u(id);
-        rv[k] = hidx_v(id);
+        const int q = maps.tuv[lane + 64 * k < NH ? lane + 64 * k : 0];
+        rt[k] = q & 255;
+        ru[k] = (q >> 8) & 255;
+        rv[k] = q >> 16;
     }
     __syncthreads();
 
