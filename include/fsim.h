@@ -281,8 +281,8 @@ fsim_status fsim_get_class_profile(fsim_ctx *ctx, fsim_class_profile *out, int32
  * 96 / 128 / 160 live values (the block is then produced in chunks that fit;
  * a budget that cannot be met falls back to variant 3), variant 3 the
  * one-wave-per-quartet kernel, variant 4 the one-lane-per-quartet kernel with
- * the primitive loops in ket-outer order (ss, ps, pp and ds bra pairs; other
- * classes run variant 1), variant 5 the one-lane-per-quartet kernel at a
+ * the primitive loops in ket-outer order (ss, ps, pp and ds bra pairs, and dp
+ * bra pairs with ss and ps kets; other classes run variant 1), variant 5 the one-lane-per-quartet kernel at a
  * budget of 192 live values for classes whose chunks do not fit 160 or that
  * need fewer chunks at 192 ((ds|pp), (dp|pp), (dp|ds); others run
  * variant 2), variant 6 the one-wave-per-quartet kernel whose two
@@ -291,11 +291,13 @@ fsim_status fsim_get_class_profile(fsim_ctx *ctx, fsim_class_profile *out, int32
  * 3).  waves_per_block is 1, 2 or 4 for launches over tiles, every K'
  * term a global atomic (variants 3 and 6 use one block shape), or 8 for the
  * segment mode of the lane variants 0, 1, 2, 4 and 5 (see
- * fsim_set_krow_lds: blocks of 8 waves (12 for the ket-outer kernel of the
- * s/p classes of total angular momentum 2), or 4 for kernels held to one wave
- * per SIMD, over segments of one bra's tiles with the bra's K' rows in LDS;
- * launches whose rows do not fit run over tiles with 4 waves per block).
- * The default is variant 1 in segment mode with 64 tiles per segment;
+ * fsim_set_krow_lds: blocks of 8 waves (12 or 16 for ket-outer kernels with
+ * few registers), or 4 for kernels held to one wave per SIMD, over segments of
+ * one bra's tiles with the bra's K' rows in LDS; launches whose rows do not fit
+ * run over tiles with 4 waves per block).  Segment launches of few tiles share
+ * each tile out over several waves and blocks.
+ * The default is variant 4 where it serves the class, variant 6 for (dd|dd) and
+ * variant 5 for the rest, in segment mode with 64 tiles per segment;
  * seg_tiles sets the segment length per class and precision (fsim_autotune
  * times 32, 64, 128 and 256 for the classes that choose segment mode). */
 typedef struct {

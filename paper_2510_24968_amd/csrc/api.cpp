@@ -484,6 +484,20 @@ static fsim_status validate(const fsim_basis *b, const fsim_options *o) {
 
 static fsim_status batched_orthogonaliser(fsim_ctx *c, hipStream_t s);
 
+// Classes the ket-outer kernel serves: ss, ps, pp and ds bras, dp bras with
+// ss and ps kets.
+static bool ko_candidate(int X, int Y) { return X <= KO_PCLASS_MAX || (X == 4 && Y <= 1); }
+
+// Kernel of a class nobody has tuned: the ket-outer one where it serves, the
+// widest bra-outer lane kernel for the other d bras, the matrix-core kernel
+// for (dd|dd).  These are the fastest or within a few per cent of it for 1 to
+// 64 waters; variant 1 everywhere, whose budget leaves (dd|pp) and (dd|dp) to
+// the one-wave-per-quartet kernel, took 10 waters 29.9 ms against 9.3.
+static int default_variant(int X, int Y) {
+    if (ko_candidate(X, Y)) return ERI_VARIANT_KO;
+    return X == NPCLASS - 1 && Y == NPCLASS - 1 ? ERI_VARIANT_MFMA : ERI_VARIANT_WIDE;
+}
+
 // Context over nmol molecules.  Shells, pairs and quartets never mix
 // molecules; every matrix is kept per molecule at a packed offset.
 static fsim_status create_impl(const fsim_basis *mols, int nmol, const fsim_options *o,
@@ -526,7 +540,7 @@ static fsim_status create_impl(const fsim_basis *mols, int nmol, const fsim_opti
     for (int X = 0; X < NPCLASS; ++X)
         for (int Y = 0; Y < NPCLASS; ++Y)
             for (int f = 0; f < 2; ++f) {
-                c->variant[X][Y][f] = ERI_DEFAULT_VARIANT;
+                c->variant[X][Y][f] = default_variant(X, Y);
                 c->wpb[X][Y][f] = 8;
                 c->segt[X][Y][f] = SEG_TILES;
                 c->tuned_ms[X][Y][f] = 0.0;
@@ -2084,10 +2098,6 @@ static bool wide_distinct(int X, int Y) {
     const int n160 = lane_chunks(X, Y, 160, &f160), n192 = lane_chunks(X, Y, 192, &f192);
     return !f160 || (f192 && n192 < n160);
 }
-
-// Classes the ket-outer kernel serves: ss, ps, pp and ds bras, dp bras with
-// ss and ps kets.
-static bool ko_candidate(int X, int Y) { return X <= KO_PCLASS_MAX || (X == 4 && Y <= 1); }
 
 extern "C" fsim_status fsim_autotune(fsim_ctx *c, const double *D, fsim_precision prec,
                                      void *stream) {

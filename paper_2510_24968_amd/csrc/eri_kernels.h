@@ -336,13 +336,67 @@ __device__ __forceinline__ void digest_chunk(const T (&out)[(A1 - A0) * ncart(LB
     }
 }
 
+// How a launch over segments shares one tile out, so that a small molecule's
+// few tiles still fill the GPU and no wave walks through all the primitives
+// of 64 quartets: csplit groups of the tile's chunks, ksplit lanes per
+// quartet, each with every ksplit-th ket primitive (a power of two up to 8; an
+// item then covers 64 / ksplit kets, and the lanes' blocks are added up
+// before the digest), and bsplit items with every bsplit-th bra primitive
+// each (the digest is linear in the block: each item digests its own share).
+struct TileShare {
+    int tile, chunk = 0, csplit = 1;
+    int k0 = 0, lane, ls = 0;   // first ket of the item in its tile, log2 ksplit
+    int b0 = 0, bstep = 1;      // bra primitives b0, b0 + bstep, ...
+    int j0 = 0, jstep = 1;      // ket primitives of the calling lane
+    __device__ __forceinline__ explicit TileShare(int t) : tile(t), lane(threadIdx.x & 63) {}
+    // item of the tiles from t0 on
+    __device__ __forceinline__ TileShare(const EriArgs &a, int t0, int item) {
+        ls = 31 - __builtin_clz(a.ksplit);
+        csplit = a.csplit;
+        bstep = a.bsplit;
+        chunk = item % csplit;
+        item /= csplit;
+        b0 = item % bstep;
+        item /= bstep;
+        k0 = (item & (a.ksplit - 1)) * (64 >> ls);
+        tile = t0 + (item >> ls);
+        lane = (threadIdx.x & 63) >> ls;
+        jstep = a.ksplit;
+        j0 = threadIdx.x & (a.ksplit - 1);
+    }
+};
+
+// Sum over the 1 << ls lanes of a quartet, in all of them (DPP: lane xor 1,
+// lane xor 2, mirrored half rows).
+template <int CTRL, typename T>
+__device__ __forceinline__ T dpp_other(T v) {
+    if constexpr (sizeof(T) == 8) {
+        return dpp_zero<CTRL>(v);
+    } else {
+        return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+    }
+}
+template <int N, int M, typename T>
+__device__ __forceinline__ void share_sum(T (&out)[N][M], int ls) {
+    if (ls == 0) return;
+#pragma unroll
+    for (int x = 0; x < N; ++x)
+#pragma unroll
+        for (int y = 0; y < M; ++y) {
+            out[x][y] += dpp_other<0xB1>(out[x][y]);
+            if (ls > 1) out[x][y] += dpp_other<0x4E>(out[x][y]);
+            if (ls > 2) out[x][y] += dpp_other<0x141>(out[x][y]);
+        }
+}
+
 // Segment mode of the lane kernels (Fock builds): the block takes whole
 // segments, each a run of tiles of one bra record, and its waves split the
 // segment's tiles.  The K' terms of a quartet all lie in the rows of the
 // bra's functions (K'_ac, K'_ad in the rows of a, K'_bc, K'_bd in those of
 // b), so they are added into the block's LDS copy of those rows; after a
 // block barrier the non-zero entries go to global K' with one atomic each
-// and the rows are cleared.  krow: (NA + NB) rows of a.kn doubles.
+// and the rows are cleared.  Short lists share their tiles out (TileShare),
+// and a.parts blocks take every parts-th item of a segment.  krow: (NA + NB) rows of a.kn doubles.
 // The block's rows after segment sg: non-zero entries added to global K'
 // and cleared (every thread of the block takes part; no barriers inside).
 template <int NA, int NB>
@@ -372,9 +426,12 @@ __device__ __forceinline__ void run_segments(const EriArgs &a, double *__restric
     const int wave = threadIdx.x >> 6, wpb = blockDim.x >> 6;
     for (int x = threadIdx.x; x < NR * a.kn; x += blockDim.x) krow[x] = 0.0;
     __syncthreads();
-    for (int sg = blockIdx.x; sg < a.tl.nseg; sg += gridDim.x) {
+    for (int w = blockIdx.x; w < a.tl.nseg * a.parts; w += gridDim.x) {
+        const int sg = w / a.parts, part = w - sg * a.parts;
         const int t0 = a.tl.seg_t0[sg], nt = a.tl.seg_nt[sg];
-        for (int t = t0 + wave; t < t0 + nt; t += wpb) body(__builtin_amdgcn_readfirstlane(t));
+        const int items = nt * a.csplit * a.ksplit * a.bsplit;
+        for (int it = wave * a.parts + part; it < items; it += wpb * a.parts)
+            body(t0, __builtin_amdgcn_readfirstlane(it));
         __syncthreads();
         segment_flush<NA, NB>(a, krow, xoff, sg);
         __syncthreads();
@@ -442,8 +499,9 @@ __global__ __launch_bounds__(SEG ? 64 * seg_waves(LA, LB, LC, LD, CA, CDC) : 256
     const long long xoff = (!STORE && a.xcd_stride) ? xcd_index() * a.xcd_stride : 0;
 
     // one tile; kl: K' rows into the block's LDS rows krow (segment mode)
-    auto tile_body = [&](const int tile, double *__restrict__ krow,
+    auto tile_body = [&](const TileShare sh, double *__restrict__ krow,
                          const bool kl) __attribute__((always_inline)) {
+        const int tile = sh.tile;
         int bra, ket;
         bool active;
         if constexpr (STORE) {
@@ -454,14 +512,18 @@ __global__ __launch_bounds__(SEG ? 64 * seg_waves(LA, LB, LC, LD, CA, CDC) : 256
         } else {
             const int b = tile_bra(a.tl, tile);
             bra = __builtin_amdgcn_readfirstlane(a.tl.bra[b]);
-            const int k0 = a.tl.ket_lo[b] + (tile - a.tl.tile_start[b]) * TILE;
-            ket = k0 + lane;
+            const int k0 = a.tl.ket_lo[b] + (tile - a.tl.tile_start[b]) * TILE + sh.k0;
+            if (k0 >= a.tl.ket_hi[b]) return;   // the whole wave: no kets in this item
+            ket = k0 + sh.lane;
             active = ket < a.tl.ket_hi[b];
             if (!active) ket = k0;
         }
         const int nbp = __builtin_amdgcn_readfirstlane(a.bra.nprim[bra]);
         const int nkp = active ? a.ket.nprim[ket] : 0;
         const bool all_staged = nbp <= ks;
+        // bra primitives are shared out only when all of them are staged
+        if (!all_staged && sh.b0 > 0) return;
+        const int bstep = all_staged ? sh.bstep : 1;
         if (STAGE && all_staged) stage(bra, 0, nbp);
         // the quartet's molecule block (bra and ket pairs share the molecule)
         const int mol = __builtin_amdgcn_readfirstlane(a.bra.mol[bra]);
@@ -490,6 +552,7 @@ __global__ __launch_bounds__(SEG ? 64 * seg_waves(LA, LB, LC, LD, CA, CDC) : 256
             f2 = __builtin_amdgcn_readfirstlane(a.bra.bf2[bra]);
             f3 = a.ket.bf1[ket];
             f4 = a.ket.bf2[ket];
+            active = active && sh.j0 == 0;   // one lane of each quartet digests
             fac = active ? 1.0 : 0.0;
             if (a.bra.sh1[bra] == a.bra.sh2[bra]) fac *= 0.5;
             if (a.ket.sh1[ket] == a.ket.sh2[ket]) fac *= 0.5;
@@ -501,13 +564,14 @@ __global__ __launch_bounds__(SEG ? 64 * seg_waves(LA, LB, LC, LD, CA, CDC) : 256
             constexpr int A0 = (ch / NCHCD) * CA, A1 = cmin(A0 + CA, NA);
             constexpr int CD0 = (ch % NCHCD) * CDC, CD1 = cmin(CD0 + CDC, NCD);
             constexpr int NAc = A1 - A0, NABc = NAc * NB, NCDc = CD1 - CD0;
+            if (NCHA * NCHCD > 1 && SEG && ch % sh.csplit != sh.chunk) return;
             T out[NABc][NCDc];
 #pragma unroll
             for (int x = 0; x < NABc; ++x)
 #pragma unroll
                 for (int y = 0; y < NCDc; ++y) out[x][y] = T(0);
 
-            for (int i = 0; i < nbp; ++i) {
+            for (int i = sh.b0; i < nbp; i += bstep) {
                 int il = i;
                 if (STAGE && !all_staged) {
                     il = i % ks;
@@ -541,15 +605,15 @@ __global__ __launch_bounds__(SEG ? 64 * seg_waves(LA, LB, LC, LD, CA, CDC) : 256
                         for (int e = 0; e < NEKC; ++e) ekn[e] = ekp[(size_t)(EK0 + e) * nk];
                     }
                 };
-                if (STAGE && nkp > 0) kload(0);
-                for (int j = 0; j < nkp; ++j) {
+                if (STAGE && sh.j0 < nkp) kload(sh.j0);
+                for (int j = sh.j0; j < nkp; j += sh.jstep) {
                     if (!STAGE) kload(j);
                     const double q = qn;
                     const double X = Px - Kxn, Y = Py - Kyn, Z = Pz - Kzn;
                     T ekc[NEKC];
 #pragma unroll
                     for (int e = 0; e < NEKC; ++e) ekc[e] = ekn[e];
-                    if (STAGE && j + 1 < nkp) kload(j + 1);
+                    if (STAGE && j + sh.jstep < nkp) kload(j + sh.jstep);
                     // 1/sqrt(p+q) once; 1/(p+q) and alpha = pq/(p+q) from it
                     T src[L + 1];
                     if constexpr (F32) {
@@ -649,6 +713,7 @@ __global__ __launch_bounds__(SEG ? 64 * seg_waves(LA, LB, LC, LD, CA, CDC) : 256
                     });
                 }
             } else {
+                if constexpr (SEG) share_sum(out, sh.ls);
                 digest_chunk<LA, LB, LC, LD, T, A0, A1, CD0, CD1>(
                     out, D, Dk, Jb, Jk, nb, nk, Kh, N, f1, f2, f3, f4, fac, active, krow, a.kn, kl);
             }
@@ -656,13 +721,13 @@ __global__ __launch_bounds__(SEG ? 64 * seg_waves(LA, LB, LC, LD, CA, CDC) : 256
     };
     if constexpr (SEG && !STORE) {
         double *__restrict__ krow = (double *)(stage_lds + (size_t)wpb * a.stage_bytes);
-        run_segments<NA, NB>(a, krow, xoff, [&](int t) __attribute__((always_inline)) {
-            tile_body(t, krow, true);
+        run_segments<NA, NB>(a, krow, xoff, [&](int t0, int it) __attribute__((always_inline)) {
+            tile_body(TileShare(a, t0, it), krow, true);
         });
     } else {
         for (int tile0 = blockIdx.x * wpb + (threadIdx.x >> 6); tile0 < ntile;
              tile0 += gridDim.x * wpb)
-            tile_body(__builtin_amdgcn_readfirstlane(tile0), nullptr, false);
+            tile_body(TileShare(__builtin_amdgcn_readfirstlane(tile0)), nullptr, false);
     }
 }
 
@@ -696,8 +761,9 @@ struct BoysTable {
 };
 
 // One tile (one bra pair x up to 64 kets) of the ket-outer kernel.
-template <int LA, int LB, int LC, int LD, typename T, bool STORE, int CA, int CDC, typename BP>
-__device__ __forceinline__ void ko_tile(const EriArgs &a, const int tile, const BP &bp,
+template <int LA, int LB, int LC, int LD, typename T, bool STORE, int CA, int CDC,
+          bool SHARED = false, typename BP>
+__device__ __forceinline__ void ko_tile(const EriArgs &a, const TileShare sh, const BP &bp,
                                         double *__restrict__ krow = nullptr, bool kl = false) {
     constexpr int L = LA + LB + LC + LD, LAB = LA + LB;
     constexpr int NA = ncart(LA), NB = ncart(LB), NC = ncart(LC), ND = ncart(LD);
@@ -706,6 +772,7 @@ __device__ __forceinline__ void ko_tile(const EriArgs &a, const int tile, const 
     constexpr int NCHA = (NA + CA - 1) / CA, NCHCD = (NCD + CDC - 1) / CDC;
     constexpr bool F32 = std::is_same<T, float>::value;
     const int lane = threadIdx.x & 63;
+    const int tile = sh.tile;
     const T *__restrict__ Sk = stab<T>(a.ket);
     const size_t nb = a.bra.n, nk = a.ket.n;
     const long long xoff = (!STORE && a.xcd_stride) ? xcd_index() * a.xcd_stride : 0;
@@ -719,8 +786,9 @@ __device__ __forceinline__ void ko_tile(const EriArgs &a, const int tile, const 
     } else {
         const int b = tile_bra(a.tl, tile);
         bra = __builtin_amdgcn_readfirstlane(a.tl.bra[b]);
-        const int k0 = a.tl.ket_lo[b] + (tile - a.tl.tile_start[b]) * TILE;
-        ket = k0 + lane;
+        const int k0 = a.tl.ket_lo[b] + (tile - a.tl.tile_start[b]) * TILE + sh.k0;
+        if (k0 >= a.tl.ket_hi[b]) return;   // the whole wave: no kets in this item
+        ket = k0 + sh.lane;
         active = ket < a.tl.ket_hi[b];
         if (!active) ket = k0;
     }
@@ -737,6 +805,7 @@ __device__ __forceinline__ void ko_tile(const EriArgs &a, const int tile, const 
     const int f1 = __builtin_amdgcn_readfirstlane(a.bra.bf1[bra]);
     const int f2 = __builtin_amdgcn_readfirstlane(a.bra.bf2[bra]);
     const int f3 = a.ket.bf1[ket], f4 = a.ket.bf2[ket];
+    if constexpr (SHARED) active = active && sh.j0 == 0;   // one lane of each quartet digests
     double fac = active ? 1.0 : 0.0;
     if (a.bra.sh1[bra] == a.bra.sh2[bra]) fac *= 0.5;
     if (a.ket.sh1[ket] == a.ket.sh2[ket]) fac *= 0.5;
@@ -763,6 +832,7 @@ __device__ __forceinline__ void ko_tile(const EriArgs &a, const int tile, const 
         constexpr int A0 = (ch / NCHCD) * CA, A1 = cmin(A0 + CA, NA);
         constexpr int CD0 = (ch % NCHCD) * CDC, CD1 = cmin(CD0 + CDC, NCD);
         constexpr int NAc = A1 - A0, NABc = NAc * NB, NCDc = CD1 - CD0;
+        if (SHARED && NCHA * NCHCD > 1 && ch % sh.csplit != sh.chunk) return;
         constexpr int EK0 = scaled_off(LC, LD, CD0), EK1 = scaled_off(LC, LD, CD1);
         T out[NABc][NCDc];
 #pragma unroll
@@ -770,7 +840,7 @@ __device__ __forceinline__ void ko_tile(const EriArgs &a, const int tile, const 
 #pragma unroll
             for (int y = 0; y < NCDc; ++y) out[x][y] = T(0);
 
-        for (int j = 0; j < nkp; ++j) {
+        for (int j = sh.j0; j < nkp; j += sh.jstep) {
             // this ket primitive, held across the bra primitives
             const double q = a.ket.p[(size_t)j * nk + ket];
             const double Kx = a.ket.P[((size_t)j * 3 + 0) * nk + ket];
@@ -781,7 +851,7 @@ __device__ __forceinline__ void ko_tile(const EriArgs &a, const int tile, const 
             const T *__restrict__ ekp = Sk + (size_t)j * NSK * nk + ket;
 #pragma unroll
             for (int e = EK0; e < EK1; ++e) ek[e - EK0] = ekp[(size_t)e * nk];
-            for (int i = 0; i < nbp; ++i) {
+            for (int i = sh.b0; i < nbp; i += sh.bstep) {
                 const double p = rp[i * 4 + 0];
                 const double X = rp[i * 4 + 1] - Kx, Y = rp[i * 4 + 2] - Ky,
                              Z = rp[i * 4 + 3] - Kz;
@@ -891,6 +961,7 @@ __device__ __forceinline__ void ko_tile(const EriArgs &a, const int tile, const 
                 });
             }
         } else {
+            if constexpr (SHARED) share_sum(out, sh.ls);
             digest_chunk<LA, LB, LC, LD, T, A0, A1, CD0, CD1>(
                 out, D, Dk, Jb, Jk, nb, nk, Kh, N, f1, f2, f3, f4, fac, active, krow, a.kn, kl);
         }
@@ -959,14 +1030,16 @@ void k_eri_lane_ko(EriArgs a) {
         // segment mode: the block's waves share the bra's K' rows
         double *__restrict__ krow = (double *)row_lds;
         const long long xoff = a.xcd_stride ? xcd_index() * a.xcd_stride : 0;
-        run_segments<ncart(LA), ncart(LB)>(a, krow, xoff, [&](int t) __attribute__((always_inline)) {
-            ko_tile<LA, LB, LC, LD, T, STORE, CA, CDC>(a, t, bp, krow, true);
-        });
+        run_segments<ncart(LA), ncart(LB)>(
+            a, krow, xoff, [&](int t0, int it) __attribute__((always_inline)) {
+                ko_tile<LA, LB, LC, LD, T, STORE, CA, CDC, true>(a, TileShare(a, t0, it), bp, krow,
+                                                                 true);
+            });
     } else {
         for (int tile0 = blockIdx.x * wpb + (threadIdx.x >> 6); tile0 < ntile;
              tile0 += gridDim.x * wpb)
-            ko_tile<LA, LB, LC, LD, T, STORE, CA, CDC>(a, __builtin_amdgcn_readfirstlane(tile0),
-                                                       bp);
+            ko_tile<LA, LB, LC, LD, T, STORE, CA, CDC>(
+                a, TileShare(__builtin_amdgcn_readfirstlane(tile0)), bp);
     }
 }
 
@@ -1041,7 +1114,9 @@ __global__ __launch_bounds__(64) void k_eri_wave(EriArgs a) {
     const T *__restrict__ Ek = etab<T>(a.ket);
     const size_t nb = a.bra.n, nk = a.ket.n;
 
-    for (int tile = blockIdx.x; tile < ntile; tile += gridDim.x) {
+    const int nsub = STORE ? 1 : a.ksplit;   // ket ranges of a tile, each an item of its own
+    for (int item = blockIdx.x; item < ntile * nsub; item += gridDim.x) {
+        const int tile = item / nsub, sub = item - tile * nsub;
         int bra, k0 = 0, k1 = 0;
         if constexpr (STORE) {
             bra = a.st_bra[tile];
@@ -1049,8 +1124,8 @@ __global__ __launch_bounds__(64) void k_eri_wave(EriArgs a) {
         } else {
             const int b = tile_bra(a.tl, tile);
             bra = a.tl.bra[b];
-            k0 = a.tl.ket_lo[b] + (tile - a.tl.tile_start[b]) * TILE;
-            k1 = min(k0 + TILE, a.tl.ket_hi[b]);
+            k0 = a.tl.ket_lo[b] + (tile - a.tl.tile_start[b]) * TILE + sub * (TILE / nsub);
+            k1 = min(k0 + TILE / nsub, a.tl.ket_hi[b]);
         }
         const int nbp = a.bra.nprim[bra];
         for (int kk = k0; kk < k1; ++kk) {
@@ -1406,7 +1481,9 @@ __global__ __launch_bounds__(64) void k_eri_mfma(EriArgs a) {
     const T *__restrict__ Ek = etab<T>(a.ket);
     const size_t nb = a.bra.n, nk = a.ket.n;
 
-    for (int tile = blockIdx.x; tile < ntile; tile += gridDim.x) {
+    const int nsub = STORE ? 1 : a.ksplit;   // ket ranges of a tile, each an item of its own
+    for (int item = blockIdx.x; item < ntile * nsub; item += gridDim.x) {
+        const int tile = item / nsub, sub = item - tile * nsub;
         int bra, k0 = 0, k1 = 0;
         if constexpr (STORE) {
             bra = a.st_bra[tile];
@@ -1414,8 +1491,8 @@ __global__ __launch_bounds__(64) void k_eri_mfma(EriArgs a) {
         } else {
             const int b = tile_bra(a.tl, tile);
             bra = a.tl.bra[b];
-            k0 = a.tl.ket_lo[b] + (tile - a.tl.tile_start[b]) * TILE;
-            k1 = min(k0 + TILE, a.tl.ket_hi[b]);
+            k0 = a.tl.ket_lo[b] + (tile - a.tl.tile_start[b]) * TILE + sub * (TILE / nsub);
+            k1 = min(k0 + TILE / nsub, a.tl.ket_hi[b]);
         }
         const int nbp = a.bra.nprim[bra];
         for (int kk = k0; kk < k1; ++kk) {
@@ -1663,18 +1740,49 @@ __host__ __device__ constexpr bool lane_fits() {
            n_chunks(LA, LB, LC, LD, BUDGET) <= MAX_CHUNKS;
 }
 
+// Launches of fewer than SHARE_WAVES tiles, three waves for every SIMD of the
+// GPU, are shared out until they have about as many items: by chunks first,
+// which repeat no work, then by ket primitives, then by bra primitives, which
+// repeat the digest.  Launch times summed, FP64: 3 waters 12.8 -> 0.79 ms, 10
+// waters 29.9 -> 6.1 ms, of which the kernels a class runs by default account
+// for the step to 3.2 and 9.3 ms.
+constexpr int SHARE_WAVES = 3072;
+inline void share_tiles(EriArgs &b, int nchunk, int waves) {
+    long long n = b.tl.ntile;
+    b.csplit = b.ksplit = b.bsplit = b.parts = 1;
+    if (n >= SHARE_WAVES) return;
+    auto want = [&] { return (int)((SHARE_WAVES + n / 2) / n); };
+    if (want() > 1) n *= b.csplit = cmin(nchunk, want());
+    while (want() > 1 && b.ksplit < 8 && b.ksplit < b.ket.kmax) {
+        b.ksplit *= 2;
+        n *= 2;
+    }
+    if (want() > 1) n *= b.bsplit = cmin(b.bra.kmax > 1 ? b.bra.kmax : 1, want());
+    // every part of a segment keeps an item for each of its waves
+    const long long per = n / b.tl.nseg / waves;
+    b.parts = per > 1 ? (int)per : 1;
+}
+
 template <int LA, int LB, int LC, int LD, typename T, bool STORE>
 void launch_wave_kernel(int ntile, const EriArgs &a, hipStream_t s) {
-    int blocks = ntile;
+    EriArgs b = a;
+    b.ksplit = 1;
+    if (!STORE)
+        while (ntile * b.ksplit < SHARE_WAVES && b.ksplit < TILE) b.ksplit *= 2;
+    int blocks = ntile * b.ksplit;
     if (blocks > 32768) blocks = 32768;
-    hipLaunchKernelGGL((k_eri_wave<LA, LB, LC, LD, T, STORE>), dim3(blocks), dim3(64), 0, s, a);
+    hipLaunchKernelGGL((k_eri_wave<LA, LB, LC, LD, T, STORE>), dim3(blocks), dim3(64), 0, s, b);
 }
 
 template <int LA, int LB, int LC, int LD, typename T, bool STORE>
 void launch_mfma_kernel(int ntile, const EriArgs &a, hipStream_t s) {
-    int blocks = ntile;
+    EriArgs b = a;
+    b.ksplit = 1;
+    if (!STORE)
+        while (ntile * b.ksplit < SHARE_WAVES && b.ksplit < TILE) b.ksplit *= 2;
+    int blocks = ntile * b.ksplit;
     if (blocks > 32768) blocks = 32768;
-    hipLaunchKernelGGL((k_eri_mfma<LA, LB, LC, LD, T, STORE>), dim3(blocks), dim3(64), 0, s, a);
+    hipLaunchKernelGGL((k_eri_mfma<LA, LB, LC, LD, T, STORE>), dim3(blocks), dim3(64), 0, s, b);
 }
 
 // LDS of one workgroup on gfx950.
@@ -1686,7 +1794,7 @@ constexpr size_t LDS_PER_CU = 160 * 1024;
 // (the caller then launches the tile-mode kernel with kn = 0) when the rows
 // do not fit next to the kernel's static LDS.
 template <int LA, int LB>
-bool segment_fit(const void *kernel, int W, EriArgs &b, int &blocks, size_t &dyn) {
+bool segment_fit(const void *kernel, int W, int nchunk, EriArgs &b, int &blocks, size_t &dyn) {
     if (b.kn <= 0 || b.tl.nseg <= 0) return false;
     const size_t rows = (size_t)(ncart(LA) + ncart(LB)) * b.kn * sizeof(double);
     hipFuncAttributes fa{};
@@ -1696,7 +1804,9 @@ bool segment_fit(const void *kernel, int W, EriArgs &b, int &blocks, size_t &dyn
     }
     dyn = (size_t)W * b.stage_bytes + rows;
     if (fa.sharedSizeBytes + dyn > LDS_PER_CU) return false;
-    blocks = b.tl.nseg < 8192 ? b.tl.nseg : 8192;
+    share_tiles(b, nchunk, W);
+    const long long n = (long long)b.tl.nseg * b.parts;
+    blocks = n < 8192 ? (int)n : 8192;
     return true;
 }
 
@@ -1704,8 +1814,7 @@ template <int LA, int LB, int LC, int LD, typename T, bool STORE, int BUDGET>
 void launch_budget(int ntile, int wpb, const EriArgs &a, hipStream_t s) {
     if constexpr (lane_fits<LA, LB, LC, LD, BUDGET>()) {
         constexpr int CA = chunk_a(LA, LB, LC, LD, BUDGET), CDC = chunk_cd(LA, LB, LC, LD, BUDGET);
-        int blocks = (ntile + wpb - 1) / wpb;
-        if (blocks > 8192) blocks = 8192;
+        int blocks = 0;
         // LDS stage of the bra primitives: up to STAGE_BYTES per wave
         constexpr int per_prim = 4 * (int)sizeof(double) + n_entries(LA, LB) * (int)sizeof(T);
         EriArgs b = a;
@@ -1718,7 +1827,8 @@ void launch_budget(int ntile, int wpb, const EriArgs &a, hipStream_t s) {
                 auto seg = k_eri_lane<LA, LB, LC, LD, T, false, CA, CDC, true>;
                 int sblocks = 0;
                 size_t dyn = 0;
-                if (segment_fit<LA, LB>((const void *)seg, W, b, sblocks, dyn)) {
+                if (segment_fit<LA, LB>((const void *)seg, W, n_chunks(LA, LB, LC, LD, BUDGET), b,
+                                        sblocks, dyn)) {
                     hipLaunchKernelGGL(seg, dim3(sblocks), dim3(64 * W), dyn, s, b);
                     return;
                 }
@@ -1747,7 +1857,9 @@ void launch_ko(int ntile, int wpb, const EriArgs &a, hipStream_t s) {
                 constexpr int W = ko_seg_waves(LA, LB, LC, LD, !std::is_same<T, float>::value);
                 int sblocks = 0;
                 size_t dyn = 0;
-                if (segment_fit<LA, LB>((const void *)seg, W, b, sblocks, dyn)) {
+                constexpr int NCH =
+                    ((ncart(LA) + CA - 1) / CA) * ((ncart(LC) * ncart(LD) + CDC - 1) / CDC);
+                if (segment_fit<LA, LB>((const void *)seg, W, NCH, b, sblocks, dyn)) {
                     hipLaunchKernelGGL(seg, dim3(sblocks), dim3(64 * W), dyn, s, b);
                     return;
                 }

@@ -81,7 +81,7 @@ __device__ __forceinline__ void persist_tile(const PersistArgs &p, int tile, con
     constexpr int X = persist_bra(SLOT), Y = persist_ket(SLOT);
     constexpr int LA = pc_l1(X), LB = pc_l2(X), LC = pc_l1(Y), LD = pc_l2(Y);
     ko_tile<LA, LB, LC, LD, T, false, ko_ca(LA, LB, LC, LD), ko_cdc(LA, LB, LC, LD)>(
-        p.cls[SLOT], tile, bp);
+        p.cls[SLOT], TileShare(tile), bp);
 }
 
 // Segment item: the block's waves split the segment's tiles, adding K' into
@@ -96,7 +96,7 @@ __device__ __forceinline__ void persist_segment(const PersistArgs &p, int sg, co
     const int t0 = a.tl.seg_t0[sg], nt = a.tl.seg_nt[sg];
     for (int t = t0 + wave; t < t0 + nt; t += wpb)
         ko_tile<LA, LB, LC, LD, T, false, ko_ca(LA, LB, LC, LD), ko_cdc(LA, LB, LC, LD)>(
-            a, __builtin_amdgcn_readfirstlane(t), bp, krow, true);
+            a, TileShare(__builtin_amdgcn_readfirstlane(t)), bp, krow, true);
     __syncthreads();
     const long long xoff = a.xcd_stride ? xcd_index() * a.xcd_stride : 0;
     segment_flush<ncart(LA), ncart(LB)>(a, krow, xoff, sg);

@@ -44,7 +44,8 @@ __global__ __launch_bounds__(SEG ? 512 : 256) void k_digest_stored(EriArgs a) {
     const int lane = threadIdx.x & 63;
     const int wpb = blockDim.x >> 6;
     const long long xoff = a.xcd_stride ? xcd_index() * a.xcd_stride : 0;
-    auto tile_body = [&](const int tile, double *__restrict__ krow,
+    // the tile's chunks c0, c0 + cstep, ...
+    auto tile_body = [&](const int tile, const int c0, const int cstep, double *__restrict__ krow,
                          const bool kl) __attribute__((always_inline)) {
         const int b = tile_bra(a.tl, tile);
         const int bra = __builtin_amdgcn_readfirstlane(a.tl.bra[b]);
@@ -74,6 +75,7 @@ __global__ __launch_bounds__(SEG ? 512 : 256) void k_digest_stored(EriArgs a) {
             constexpr int A0 = (ch / NCHCD) * CA, A1 = cmin(A0 + CA, NA);
             constexpr int CD0 = (ch % NCHCD) * CDC, CD1 = cmin(CD0 + CDC, NCD);
             constexpr int NABc = (A1 - A0) * NB, NCDc = CD1 - CD0;
+            if (NCHA * NCHCD > 1 && ch % cstep != c0) return;
             double out[NABc][NCDc];
             static_for<NABc>([&](auto abl_) {
                 constexpr int abl = decltype(abl_)::value;
@@ -91,13 +93,14 @@ __global__ __launch_bounds__(SEG ? 512 : 256) void k_digest_stored(EriArgs a) {
     if constexpr (SEG) {
         extern __shared__ __align__(16) unsigned char row_lds[];
         double *__restrict__ krow = (double *)row_lds;
-        run_segments<NA, NB>(a, krow, xoff, [&](int t) __attribute__((always_inline)) {
-            tile_body(t, krow, true);
+        run_segments<NA, NB>(a, krow, xoff, [&](int t0, int it) __attribute__((always_inline)) {
+            const int nch = a.csplit;
+            tile_body(t0 + it / nch, it % nch, nch, krow, true);
         });
     } else {
         for (int tile0 = blockIdx.x * wpb + (threadIdx.x >> 6); tile0 < a.tl.ntile;
              tile0 += gridDim.x * wpb)
-            tile_body(__builtin_amdgcn_readfirstlane(tile0), nullptr, false);
+            tile_body(__builtin_amdgcn_readfirstlane(tile0), 0, 1, nullptr, false);
     }
 }
 
@@ -108,10 +111,14 @@ static hipError_t launch_digest(int wpb, const EriArgs &a, hipStream_t s) {
     if (a.kn > 0 && a.tl.nseg > 0) {
         EriArgs b = a;
         b.stage_bytes = 0;
+        b.ket.kmax = b.bra.kmax = 1;   // nothing but the chunks to share out
+        constexpr int CA = digest_chunk_a(LA, LB, LC, LD), CDC = digest_chunk_cd(LA, LB, LC, LD);
+        constexpr int NCH =
+            ((ncart(LA) + CA - 1) / CA) * ((ncart(LC) * ncart(LD) + CDC - 1) / CDC);
         int blocks = 0;
         size_t dyn = 0;
         auto seg = k_digest_stored<LA, LB, LC, LD, true>;
-        if (segment_fit<LA, LB>((const void *)seg, 8, b, blocks, dyn)) {
+        if (segment_fit<LA, LB>((const void *)seg, 8, NCH, b, blocks, dyn)) {
             hipLaunchKernelGGL(seg, dim3(blocks), dim3(512), dyn, s, b);
             return hipGetLastError();
         }
