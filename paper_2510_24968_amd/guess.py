@@ -353,7 +353,10 @@ class GuessNet:
         """Masked mean-square loss (device scalar) and FP32 gradients."""
         n = Xb.shape[0]
         Y, (acts, outs) = self.forward(Xb)
-        loss = torch.zeros(1, dtype=torch.float32, device=self.dev)
+        # loss and weight gradients are added up into one cleared buffer
+        sizes = [i * o for i, o in self.dims]
+        loss, *dWf = torch.zeros(1 + sum(sizes), dtype=torch.float32,
+                                 device=self.dev).split([1] + sizes)
         g = torch.empty_like(Y)
         cnt = max(float(mask.sum().item()), 1.0)
         _chk(_lib().fsim_mse(Y.numel(), _p(Y), _p(T), _p(mask), 1.0 / cnt, _p(g), _p(loss),
@@ -363,7 +366,7 @@ class GuessNet:
         dW, db = [None] * 3, [None] * 3
         for k in (2, 1, 0):
             i, o = self.dims[k]
-            dW[k] = torch.zeros(i, o, dtype=torch.float32, device=self.dev)
+            dW[k] = dWf[k].view(i, o)
             self.gemm(i, o, n, acts[k], i, 1, gb, o, 0, C=dW[k], ksplit=ks)        # act^T g
             db[k] = torch.empty(o, dtype=torch.float32, device=self.dev)
             _chk(_lib().fsim_bias_grad(n, o, _p(g), _p(db[k]), _stream()))

@@ -1,8 +1,9 @@
 """fsim_gemm_bf16 where its 16-byte loads may not be used: operands that start
-or step off a vector boundary, and sizes around its 64-wide tiles and stages.
+or step off a vector boundary, and sizes around its 64-wide tiles and stages;
+fsim_bias_grad around its 512-row splits and 32-column blocks.
 
-Against a float64 product of the same BF16 values: K 2^-23 (|A| |B|), the
-rounding of K float32 additions."""
+Against float64 results of the same values: K 2^-23 (|A| |B|), the rounding of
+K float32 additions, and likewise n 2^-23 sum |dY| for the column sums."""
 
 import numpy as np
 import pytest
@@ -36,3 +37,19 @@ def test_offsets_and_pitches(off, pad, ta, tb):
         bound = K * 2.0 ** -23 * (a.abs() @ b.abs()).numpy() + 1e-30
         err = np.abs(C.double().cpu().numpy() - ref)
         assert np.all(err <= bound), (M, N, K, ks, float((err / bound).max()))
+
+
+@pytest.mark.parametrize("n", [1, 127, 128, 511, 512, 513, 5000])
+def test_column_sums(n):
+    import ctypes
+    from paper_2510_24968_amd import guess
+    for m in (1, 31, 33, 256):
+        g = torch.Generator().manual_seed(n + m)
+        dY = torch.randn(n, m, generator=g)
+        db = torch.full((m,), float("nan"), dtype=torch.float32, device="cuda")
+        d = dY.cuda()
+        ptr = lambda t: ctypes.c_void_p(t.data_ptr())
+        s = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+        assert guess._lib().fsim_bias_grad(n, m, ptr(d), ptr(db), s) == 0
+        err = (db.double().cpu() - dY.double().sum(0)).abs()
+        assert torch.all(err <= n * 2.0 ** -23 * dY.double().abs().sum(0) + 1e-30), (n, m)
