@@ -13,6 +13,7 @@
 #include <map>
 #include <numeric>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/fsim.h"
@@ -138,6 +139,7 @@ struct fsim_ctx {
     long long *d_mol_off = nullptr;
     double *Emol = nullptr;           // [nmol] electronic energies of the last build
     std::vector<double> Emol_host;
+    double *Emol_pin = nullptr;       // pinned landing place of Emol
     // batched SCF (nmol > 1): zero-padded N_max x N_max blocks
     double *pS = nullptr, *pX = nullptr, *pH = nullptr, *pF = nullptr, *pD = nullptr,
            *pT1 = nullptr, *pT2 = nullptr, *pEig = nullptr, *pErr = nullptr, *pRed = nullptr;
@@ -154,6 +156,11 @@ struct fsim_ctx {
     bool krow_lds = true;
     // tiles per segment, per class and precision (tuning)
     int segt[NPCLASS][NPCLASS][2];
+    // side streams of the class launches, joined to the build's stream
+    // before and after (created by the first build that may create them)
+    static constexpr int NSIDE = 3;
+    hipStream_t side[NSIDE] = {};
+    hipEvent_t fork_ev = nullptr, join_ev[NSIDE] = {};
     // captured Fock build (hipGraph), one per precision
     bool graph_enabled = false;
     hipStream_t gstream = nullptr;
@@ -273,25 +280,38 @@ static fsim_status alloc_table(DevPool &pool, PairTable &t, int l1, int l2, int 
     t.kmax = kmax;
     t.ne = n_entries(l1, l2);
     if (n == 0) return FSIM_OK;
-    HIPCHK(pool.alloc(&t.sh1, n));
-    HIPCHK(pool.alloc(&t.sh2, n));
-    HIPCHK(pool.alloc(&t.bf1, n));
-    HIPCHK(pool.alloc(&t.bf2, n));
-    HIPCHK(pool.alloc(&t.nprim, n));
-    HIPCHK(pool.alloc(&t.mol, n));
-    HIPCHK(pool.alloc(&t.Q, n));
-    HIPCHK(pool.alloc(&t.p, (size_t)kmax * n));
-    HIPCHK(pool.alloc(&t.P, (size_t)kmax * 3 * n));
-    HIPCHK(pool.alloc(&t.E, (size_t)kmax * t.ne * n));
-    HIPCHK(pool.alloc(&t.Ef, (size_t)kmax * t.ne * n));
-    HIPCHK(pool.alloc(&t.rp, (size_t)kmax * 4 * n));
-    HIPCHK(pool.alloc(&t.rE, (size_t)kmax * t.ne * n));
-    HIPCHK(pool.alloc(&t.rEf, (size_t)kmax * t.ne * n));
-    if (pclass(l1, l2) <= KO_PCLASS_MAX) {
-        const size_t ns = (size_t)kmax * n_scaled(l1, l2) * n;
-        HIPCHK(pool.alloc(&t.S0, (size_t)kmax * n));
-        HIPCHK(pool.alloc(&t.S, ns));
-        HIPCHK(pool.alloc(&t.Sf, ns));
+    // one allocation per table, carved at 256-byte boundaries
+    const size_t N = n, K = kmax, NE = t.ne;
+    const bool ko = pclass(l1, l2) <= KO_PCLASS_MAX;
+    const size_t NS = ko ? K * n_scaled(l1, l2) * N : 0;
+    char *base = nullptr;
+    size_t at = 0;
+    for (int pass = 0; pass < 2; ++pass) {
+        at = 0;
+        auto take = [&](auto **p, size_t count) {
+            if (pass) *p = (std::remove_reference_t<decltype(**p)> *)(base + at);
+            at += (count * sizeof(**p) + 255) / 256 * 256;
+        };
+        take(&t.sh1, N);
+        take(&t.sh2, N);
+        take(&t.bf1, N);
+        take(&t.bf2, N);
+        take(&t.nprim, N);
+        take(&t.mol, N);
+        take(&t.Q, N);
+        take(&t.p, K * N);
+        take(&t.P, K * 3 * N);
+        take(&t.E, K * NE * N);
+        take(&t.Ef, K * NE * N);
+        take(&t.rp, K * 4 * N);
+        take(&t.rE, K * NE * N);
+        take(&t.rEf, K * NE * N);
+        if (ko) {
+            take(&t.S0, K * N);
+            take(&t.S, NS);
+            take(&t.Sf, NS);
+        }
+        if (!pass) HIPCHK(pool.alloc(&base, at));
     }
     return FSIM_OK;
 }
@@ -647,6 +667,7 @@ static fsim_status create_impl(const fsim_basis *mols, int nmol, const fsim_opti
     PCHK(c->pool.alloc(&c->d_nocc, nmol));
     HCHK(up(c->d_nocc, c->mol_nocc.data(), sizeof(int) * nmol));
     PCHK(c->pool.alloc(&c->Emol, nmol));
+    PCHK(hipHostMalloc((void **)&c->Emol_pin, sizeof(double) * nmol, hipHostMallocDefault));
     HCHK(launch_shell_norm(sh, nullptr));
     PCHK(c->pool.alloc(&c->boys, (size_t)BOYS_TOTAL));
     HCHK(launch_boys_table(c->boys, nullptr));
@@ -816,7 +837,13 @@ extern "C" fsim_status fsim_ctx_destroy(fsim_ctx *c) {
         if (c->gev[p]) hipEventDestroy(c->gev[p]);
     }
     if (c->gstream) hipStreamDestroy(c->gstream);
+    for (int k = 0; k < fsim_ctx::NSIDE; ++k) {
+        if (c->side[k]) hipStreamDestroy(c->side[k]);
+        if (c->join_ev[k]) hipEventDestroy(c->join_ev[k]);
+    }
+    if (c->fork_ev) hipEventDestroy(c->fork_ev);
     for (auto &e : c->ev) hipEventDestroy(e);
+    if (c->Emol_pin) hipHostFree(c->Emol_pin);
     c->store_pool.clear();
     c->screen_pool.clear();
     c->pool.clear();
@@ -1342,6 +1369,7 @@ static void drop_graphs(fsim_ctx *c) {
 }
 
 static constexpr int NXCD = 8;   // XCDs of an MI355X
+static constexpr size_t ASSEMBLE_COPIES_MAX = 1 << 14;
 
 // Persistent queue slots (as persistent.hip orders them) and the class record
 // the profile uses for the persistent launch.
@@ -1363,13 +1391,76 @@ struct AccPair {
 // dref (optional): an incremental build over the density-screened lists;
 // D is then D - Dref and J, K (required) become Jref + J[D], Kref + K[D].
 struct DeltaRefs {
-    const double *J, *K;
+    const double *J, *K, *D;   // references, and the whole density
+};
+
+// Launches of a build: classes with tiles, per precision part (the lists of a
+// full build bound those of an incremental one).
+static int class_launches(const fsim_ctx *c, bool mixed) {
+    int n = 0;
+    for (int X = 0; X < NPCLASS; ++X)
+        for (int Y = 0; Y <= X; ++Y) {
+            const ClassLists &cl = c->lists[X][Y];
+            n += mixed ? (cl.mix64.ntile > 0) + (cl.mix32.ntile > 0) : cl.all64.ntile > 0;
+        }
+    return n;
+}
+
+static fsim_status ensure_side_streams(fsim_ctx *c, bool mixed) {
+    if (c->fork_ev || class_launches(c, mixed) < 2) return FSIM_OK;
+    for (int k = 0; k < fsim_ctx::NSIDE; ++k) {
+        if (!c->side[k]) HIPCHK(hipStreamCreateWithFlags(&c->side[k], hipStreamNonBlocking));
+        if (!c->join_ev[k]) HIPCHK(hipEventCreateWithFlags(&c->join_ev[k], hipEventDisableTiming));
+    }
+    HIPCHK(hipEventCreateWithFlags(&c->fork_ev, hipEventDisableTiming));
+    return FSIM_OK;
+}
+
+// The class launches of one build over the build's stream and the side
+// streams, each on the one with the least work so far.  A launch ends with a
+// few long tiles on an otherwise idle GPU, and a small molecule's launches
+// never fill it: side by side they overlap (3 waters 0.81 -> 0.55 ms, 10 waters
+// 6.12 -> 4.84).
+// Builds that are profiled, or have one launch, stay on their stream.
+struct LaunchStreams {
+    fsim_ctx *c;
+    hipStream_t s;
+    int n = 1;
+    double load[1 + fsim_ctx::NSIDE] = {};
+
+    LaunchStreams(fsim_ctx *ctx, hipStream_t stream) : c(ctx), s(stream) {}
+    ~LaunchStreams() { (void)join(); }   // also when a launch failed in between
+
+    fsim_status fork(int launches, bool allowed) {
+        if (!allowed || launches < 2 || !c->fork_ev) return FSIM_OK;
+        n = std::min(launches, 1 + fsim_ctx::NSIDE);
+        HIPCHK(hipEventRecord(c->fork_ev, s));
+        for (int k = 0; k + 1 < n; ++k) HIPCHK(hipStreamWaitEvent(c->side[k], c->fork_ev, 0));
+        return FSIM_OK;
+    }
+    hipStream_t next(double work) {
+        int k = 0;
+        for (int i = 1; i < n; ++i)
+            if (load[i] < load[k]) k = i;
+        load[k] += work;
+        return k == 0 ? s : c->side[k - 1];
+    }
+    fsim_status join() {
+        for (int k = 0; k + 1 < n; ++k) {
+            HIPCHK(hipEventRecord(c->join_ev[k], c->side[k]));
+            HIPCHK(hipStreamWaitEvent(s, c->join_ev[k], 0));
+        }
+        n = 1;
+        return FSIM_OK;
+    }
 };
 
 static fsim_status enqueue_build(fsim_ctx *c, const double *D, double *F, double *J, double *K,
                                  bool mixed, std::vector<fsim_class_profile> *prof,
                                  hipStream_t s, const AccPair *acc = nullptr,
                                  const DeltaRefs *dref = nullptr) {
+    // the density of the energy, left in c->Emol when there is an F
+    const double *De = dref ? dref->D : D;
     const size_t P = (size_t)c->packed;
     const bool xp = !acc && c->xcd_private && c->priv;
     double *Jsum = acc ? acc->J : c->Jh, *Ksum = acc ? acc->K : c->Kh;
@@ -1378,9 +1469,10 @@ static fsim_status enqueue_build(fsim_ctx *c, const double *D, double *F, double
     // J' in pair order: the first PJ entries of each copy
     const size_t PJ = (size_t)c->pj_off[NPCLASS];
     if (xp)
-        HIPCHK(begin_build(c->priv, 2 * NXCD * P, nullptr, 0, PJ, c->pj_src, D, c->Dp, s));
+        HIPCHK(begin_build(c->priv, 2 * NXCD * P, nullptr, 0, c->Emol, c->nmol, PJ, c->pj_src, D,
+                           c->Dp, s));
     else
-        HIPCHK(begin_build(Jsum, PJ, Ksum, P, PJ, c->pj_src, D, c->Dp, s));
+        HIPCHK(begin_build(Jsum, PJ, Ksum, P, c->Emol, c->nmol, PJ, c->pj_src, D, c->Dp, s));
     int nev = 0;
     // s/p classes through the persistent queue kernel (the stored-integral
     // digest has its own kernel)
@@ -1389,6 +1481,8 @@ static fsim_status enqueue_build(fsim_ctx *c, const double *D, double *F, double
     bool have_pa[2] = {false, false};
     const int maxn = *std::max_element(c->mol_n.begin(), c->mol_n.end());
     if (persist) HIPCHK(fill_int(c->pcounter, 2, 0, s));
+    LaunchStreams ls(c, s);
+    STCHK(ls.fork(class_launches(c, mixed), !prof && !persist));
     // heaviest classes (highest L) first
     for (int X = NPCLASS - 1; X >= 0; --X)
         for (int Y = X; Y >= 0; --Y) {
@@ -1457,16 +1551,20 @@ static fsim_status enqueue_build(fsim_ctx *c, const double *D, double *F, double
                 a.boys = c->boys;
                 a.kn = c->krow_lds && tl.nseg > 0 ? maxn : 0;
                 const int f32 = mixed && part == 1;
+                const ListStats &st = mixed ? (part == 0 ? cl.sm64 : cl.sm32) : cl.s64;
+                // a launch costs at least its latency, some 1e8 of these operations
+                hipStream_t sl = ls.next(st.flops_exec + 1e8);
                 if (c->stored && !dref) {
                     a.out = c->store + c->store_off[X][Y];
-                    HIPCHK(launch_digest_stored(X, Y, 4, a, s));
+                    HIPCHK(launch_digest_stored(X, Y, 4, a, sl));
                 } else {
                     HIPCHK(launch_eri(X, Y, f32, false, c->variant[X][Y][f32], c->wpb[X][Y][f32],
-                                      a, s));
+                                      a, sl));
                 }
                 if (prof) HIPCHK(hipEventRecord(c->ev[nev++], s));
             }
         }
+    STCHK(ls.join());
     for (int part = 0; part < 2; ++part) {
         if (!have_pa[part]) continue;
         PersistArgs &q = pa[part];
@@ -1516,26 +1614,25 @@ static fsim_status enqueue_build(fsim_ctx *c, const double *D, double *F, double
         HIPCHK(launch_persistent(mixed && part == 1, q, s));
         if (prof) HIPCHK(hipEventRecord(c->ev[nev++], s));
     }
-    if (xp) {
+    // the copies of small matrices are summed by the assembly itself (it reads
+    // every element twice)
+    Accum sums{Jsum, Ksum, c->pj_pos, 1, 0};
+    if (xp && P <= ASSEMBLE_COPIES_MAX)
+        sums = Accum{c->priv, c->priv + NXCD * P, c->pj_pos, NXCD, P};
+    else if (xp)
         HIPCHK(sum_copies2(NXCD, P, PJ, c->priv, Jsum, P, c->priv + NXCD * P, Ksum, s));
-    }
-    if (dref)
-        HIPCHK(assemble_delta(layout_of(c), Jsum, c->pj_pos, Ksum, c->H, dref->J, dref->K, F, J, K, s));
-    else
-        HIPCHK(assemble_fock_packed(layout_of(c), Jsum, c->pj_pos, Ksum, c->H, F, J, K, s));
+    HIPCHK(assemble(layout_of(c), sums, c->H, dref ? dref->J : nullptr, dref ? dref->K : nullptr, F,
+                    J, K, De, F ? c->Emol : nullptr, s));
     return FSIM_OK;
 }
 
-// E_elec = 1/2 Tr[D (H + F)] summed over the molecules (synchronises s).
-static fsim_status electronic_energy(fsim_ctx *c, const double *D, const double *F, double *E,
-                                     hipStream_t s) {
-    HIPCHK(fill(c->Emol, c->nmol, 0.0, s));
-    HIPCHK(dot3_packed(layout_of(c), D, c->H, F, 0.5, c->Emol, s));
-    HIPCHK(hipMemcpyAsync(c->Emol_host.data(), c->Emol, sizeof(double) * c->nmol,
-                          hipMemcpyDeviceToHost, s));
+// The electronic energies the assembly left on the device, summed over the
+// molecules (synchronises s).
+static fsim_status electronic_energy(fsim_ctx *c, double *E, hipStream_t s) {
+    HIPCHK(hipMemcpyAsync(c->Emol_pin, c->Emol, sizeof(double) * c->nmol, hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
     double e = 0.0;
-    for (double v : c->Emol_host) e += v;
+    for (int m = 0; m < c->nmol; ++m) e += c->Emol_host[m] = c->Emol_pin[m];
     *E = e;
     return FSIM_OK;
 }
@@ -1552,6 +1649,7 @@ static fsim_status fock_build_sph(fsim_ctx *c, const double *D, double *F, doubl
         c->ev.resize(2 * 2 * NPCLASS * NPCLASS);
         for (auto &e : c->ev) HIPCHK(hipEventCreate(&e));
     }
+    STCHK(ensure_side_streams(c, mixed));
     if (c->xcd_private && !c->priv) HIPCHK(c->pool.alloc(&c->priv, 2 * NXCD * (size_t)c->packed));
     std::vector<fsim_class_profile> prof;
     STCHK(enqueue_build(c, c->Dc, nullptr, c->Jc, c->Kc, mixed, c->profiling ? &prof : nullptr, s));
@@ -1592,6 +1690,7 @@ static fsim_status fock_build(fsim_ctx *c, const double *D, double *F, double *J
         c->ev.resize(2 * 2 * NPCLASS * NPCLASS);
         for (auto &e : c->ev) HIPCHK(hipEventCreate(&e));
     }
+    STCHK(ensure_side_streams(c, mixed));
     if (c->xcd_private && !c->priv) HIPCHK(c->pool.alloc(&c->priv, 2 * NXCD * P));
     const bool use_graph = c->graph_enabled && !c->profiling && !J && !K && F;
     if (use_graph) {
@@ -1640,7 +1739,7 @@ static fsim_status fock_build(fsim_ctx *c, const double *D, double *F, double *J
     }
     if (E_elec) {
         if (!F) return fail(FSIM_EINVAL, "E_elec needs F");
-        STCHK(electronic_energy(c, D, F, E_elec, s));
+        STCHK(electronic_energy(c, E_elec, s));
     }
     return FSIM_OK;
 }
@@ -1672,7 +1771,7 @@ extern "C" fsim_status fsim_fock_build_noalloc(fsim_ctx *c, const double *D, dou
     if (!Fo && E_elec) Fo = c->F;   // context-owned, allocated at create
     const AccPair acc{c->noalloc, c->noalloc + NOALLOC_MAX_PACKED};
     STCHK(enqueue_build(c, D, Fo, J, K, prec == FSIM_MIXED && c->tau32 > 0, nullptr, s, &acc));
-    if (E_elec) STCHK(electronic_energy(c, D, Fo, E_elec, s));
+    if (E_elec) STCHK(electronic_energy(c, E_elec, s));
     return FSIM_OK;
 }
 
@@ -1886,9 +1985,10 @@ static fsim_status fock_build_delta_impl(fsim_ctx *c, const double *D, const dou
         c->ev.resize(2 * 2 * NPCLASS * NPCLASS);
         for (auto &e : c->ev) HIPCHK(hipEventCreate(&e));
     }
+    STCHK(ensure_side_streams(c, mixed));
     if (c->xcd_private && !c->priv) HIPCHK(c->pool.alloc(&c->priv, 2 * NXCD * (size_t)c->packed));
     std::vector<fsim_class_profile> prof;
-    const DeltaRefs dref{Jref, Kref};
+    const DeltaRefs dref{Jref, Kref, D};
     STCHK(enqueue_build(c, c->dD, F, J, K, mixed, c->profiling ? &prof : nullptr, s, nullptr,
                         &dref));
     if (c->profiling) {
@@ -1901,7 +2001,7 @@ static fsim_status fock_build_delta_impl(fsim_ctx *c, const double *D, const dou
         c->prof = prof;
     }
     if (quartets) *quartets = nq;
-    if (E_elec) STCHK(electronic_energy(c, D, F, E_elec, s));
+    if (E_elec) STCHK(electronic_energy(c, E_elec, s));
     return FSIM_OK;
 }
 

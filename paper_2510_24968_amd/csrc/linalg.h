@@ -15,9 +15,9 @@ struct DiisPtrs {
 
 hipError_t fill(double *x, size_t n, double v, hipStream_t s);
 hipError_t fill_int(int *x, size_t n, int v, hipStream_t s);
-// z0[0..n0) = z1[0..n1) = 0 and dst[i] = src[idx[i]] for i < n
-hipError_t begin_build(double *z0, size_t n0, double *z1, size_t n1, size_t n, const int *idx,
-                       const double *src, double *dst, hipStream_t s);
+// z0[0..n0) = z1[0..n1) = z2[0..n2) = 0 and dst[i] = src[idx[i]] for i < n
+hipError_t begin_build(double *z0, size_t n0, double *z1, size_t n1, double *z2, size_t n2,
+                       size_t n, const int *idx, const double *src, double *dst, hipStream_t s);
 // dK[i] = sum_{k < ncopy} sK[k * stride + i] for i < nK, K = 0, 1
 hipError_t sum_copies2(int ncopy, size_t stride, size_t n0, const double *s0, double *d0,
                        size_t n1, const double *s1, double *d1, hipStream_t s);
@@ -37,16 +37,21 @@ struct MolLayout {
     const long long *off = nullptr;   // [nmol]
     const int *n = nullptr;           // [nmol]
 };
-// J = J' + J'^T, K = Kh + Kh^T, F = H + J - K/2 per block; J' of matrix
-// element x is Jp[pos[x]] (0 where pos[x] < 0)
-hipError_t assemble_fock_packed(const MolLayout &L, const double *Jp, const int *pos,
-                                const double *Kh,
-                                const double *H, double *F, double *J, double *K, hipStream_t s);
-// J = Jref + J' + J'^T, K = Kref + Kh + Kh^T, F = H + J - K/2 per block (F may
-// be NULL; J may alias Jref, K may alias Kref)
-hipError_t assemble_delta(const MolLayout &L, const double *Jp, const int *pos,
-                          const double *Kh, const double *H, const double *Jref, const double *Kref, double *F, double *J, double *K,
-                          hipStream_t s);
+// J' and K' half-sums of a build: ncopy copies of each, stride elements
+// apart; J' in pair order (J' of matrix element x is J[pos[x]], 0 where
+// pos[x] < 0).
+struct Accum {
+    const double *J = nullptr, *K = nullptr;
+    const int *pos = nullptr;
+    int ncopy = 1;
+    size_t stride = 0;
+};
+// per block: J = Jref + J' + J'^T, K = Kref + K' + K'^T (no references: NULL;
+// J may alias Jref, K may alias Kref), F = H + J - K/2, and E[m] += 1/2
+// Tr[D (H + F)]; F, J, K and E may be NULL, E needs F
+hipError_t assemble(const MolLayout &L, const Accum &acc, const double *H, const double *Jref,
+                    const double *Kref, double *F, double *J, double *K, const double *D, double *E,
+                    hipStream_t s);
 // out = (A + A^T) / 2 (N x N; out must not alias A)
 hipError_t symmetrize(int N, const double *A, double *out, hipStream_t s);
 // J = (Jr + Jr^T)/2, K = (Kr + Kr^T)/2, F = H + J - K/2 (N x N; outputs may be
@@ -57,9 +62,6 @@ hipError_t assemble_sym(int N, const double *Jr, const double *Kr, const double 
 // (a, b), by bit-pattern atomics on M (which must hold zeros on entry)
 hipError_t delta_blockmax(int N, const double *D, const double *Dref, double *dD,
                           const int *bf_shell, int ns, double *M, hipStream_t s);
-// E[m] += w * sum_block A (B + C)
-hipError_t dot3_packed(const MolLayout &L, const double *A, const double *B, const double *C,
-                       double w, double *E, hipStream_t s);
 // padded <- packed, with `diag` on the padding diagonal
 hipError_t pad_blocks(const MolLayout &L, const double *packed, double *padded, double diag,
                       hipStream_t s);

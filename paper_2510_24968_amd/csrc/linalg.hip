@@ -15,16 +15,19 @@ __global__ void k_fill_int(int *x, size_t n, int v) {
         x[i] = v;
 }
 
-// Start of a Fock build: both accumulators cleared and the density gathered
-// into pair order, in one launch (a small molecule's build is a few launches
-// of some 5 us each: 8 H atoms 93 -> 74 us with this and k_sum_copies2).
-__global__ void k_begin_build(double *z0, size_t n0, double *z1, size_t n1, size_t n,
-                              const int *__restrict__ idx, const double *__restrict__ src,
-                              double *__restrict__ dst) {
+// Start of a Fock build: the accumulators and the energies cleared and the
+// density gathered into pair order, in one launch (a small molecule's build is
+// a few launches of some 5 us each: 8 H atoms 93 -> 74 us with this and
+// k_sum_copies2, 46 -> 39 us with the energy and, for small matrices, the
+// copy sums taken into the assembly).
+__global__ void k_begin_build(double *z0, size_t n0, double *z1, size_t n1, double *z2, size_t n2,
+                              size_t n, const int *__restrict__ idx,
+                              const double *__restrict__ src, double *__restrict__ dst) {
     const size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
     const size_t step = (size_t)gridDim.x * blockDim.x;
     for (size_t i = t; i < n0; i += step) z0[i] = 0.0;
     for (size_t i = t; i < n1; i += step) z1[i] = 0.0;
+    for (size_t i = t; i < n2; i += step) z2[i] = 0.0;
     for (size_t i = t; i < n; i += step) dst[i] = src[idx[i]];
 }
 
@@ -44,12 +47,32 @@ __global__ void k_sum_copies2(int ncopy, size_t stride, size_t n0, const double 
     }
 }
 
+// Sum of element x over the copies of an accumulator.
+__device__ __forceinline__ double copies_sum(const double *__restrict__ A, int ncopy,
+                                             size_t stride, size_t x) {
+    double v = A[x];
+    for (int k = 1; k < ncopy; ++k) v += A[k * stride + x];
+    return v;
+}
 // J' of matrix element x from the pair-ordered sums: 0 where x names no
 // stored element (a dropped pair, or the transpose of a stored one).
-__device__ __forceinline__ double pair_value(const double *__restrict__ Jp,
-                                             const int *__restrict__ pos, size_t x) {
-    const int o = pos[x];
-    return o >= 0 ? Jp[o] : 0.0;
+__device__ __forceinline__ double pair_value(const Accum &acc, size_t x) {
+    const int o = acc.pos[x];
+    return o >= 0 ? copies_sum(acc.J, acc.ncopy, acc.stride, o) : 0.0;
+}
+__device__ __forceinline__ double k_value(const Accum &acc, size_t x) {
+    return copies_sum(acc.K, acc.ncopy, acc.stride, x);
+}
+// *E += the block's sum of v
+__device__ __forceinline__ void block_add(double v, double *E) {
+    __shared__ double red[256];
+    red[threadIdx.x] = v;
+    __syncthreads();
+    for (int o = blockDim.x / 2; o > 0; o >>= 1) {
+        if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) atomicAdd(E, red[0]);
 }
 
 // Block-reduced sum of w * sum_x A[x] * (B[x] + C[x]) (C may be NULL) into *out.
@@ -127,43 +150,35 @@ __global__ void k_lincomb(size_t n, int m, DiisPtrs P, double *out) {
 // ---------------------------------------------------------------------------
 // packed / padded per-molecule kernels: grid.y runs over molecules
 // ---------------------------------------------------------------------------
-// J = J' + J'^T, K = K' + K'^T, F = H + J - K/2 (Eq. fock, G = J - K/2), J'
-// in pair order (pos: where each matrix element's J' is kept, -1 if nowhere).
-__global__ void k_assemble_packed(MolLayout L, const double *__restrict__ Jp,
-                                  const int *__restrict__ pos, const double *__restrict__ Kh, const double *__restrict__ H,
-                                  double *F, double *J, double *K) {
+// J = Jref + J' + J'^T, K = Kref + K' + K'^T, F = H + J - K/2 (Eq. fock,
+// G = J - K/2), and the electronic energy 1/2 Tr[D (H + F)] added to E[m].
+// Jref, Kref: NULL or the references of an incremental build (which J, K may
+// alias); F, J, K: NULL or outputs; E needs F.
+__global__ void k_assemble(MolLayout L, Accum acc, const double *__restrict__ H, const double *Jref,
+                           const double *Kref, double *F, double *J, double *K,
+                           const double *__restrict__ D, double *E) {
     const int m = blockIdx.y, n = L.n[m];
     const size_t base = L.off[m], n2 = (size_t)n * n;
+    double e = 0.0;
     for (size_t x = blockIdx.x * (size_t)blockDim.x + threadIdx.x; x < n2;
          x += (size_t)gridDim.x * blockDim.x) {
         const size_t i = x / n, j = x - i * n;
         const size_t a = base + x, at = base + j * n + i;
-        const double jj = pair_value(Jp, pos, a) + pair_value(Jp, pos, at);
-        const double kk = Kh[a] + Kh[at];
-        if (F) F[a] = H[a] + jj - 0.5 * kk;
+        double jj = pair_value(acc, a) + pair_value(acc, at);
+        double kk = k_value(acc, a) + k_value(acc, at);
+        if (Jref) {
+            jj = Jref[a] + jj;
+            kk = Kref[a] + kk;
+        }
+        if (F) {
+            const double h = H[a], f = h + jj - 0.5 * kk;
+            F[a] = f;
+            if (E) e += 0.5 * D[a] * (h + f);
+        }
         if (J) J[a] = jj;
         if (K) K[a] = kk;
     }
-}
-
-// Incremental build: J = Jref + J'_d + J'_d^T, K = Kref + K'_d + K'_d^T,
-// F = H + J - K/2 (J may alias Jref and K may alias Kref).
-__global__ void k_assemble_delta(MolLayout L, const double *__restrict__ Jp,
-                                 const int *__restrict__ pos, const double *__restrict__ Kh, const double *__restrict__ H,
-                                 const double *Jref, const double *Kref, double *F, double *J,
-                                 double *K) {
-    const int m = blockIdx.y, n = L.n[m];
-    const size_t base = L.off[m], n2 = (size_t)n * n;
-    for (size_t x = blockIdx.x * (size_t)blockDim.x + threadIdx.x; x < n2;
-         x += (size_t)gridDim.x * blockDim.x) {
-        const size_t i = x / n, j = x - i * n;
-        const size_t a = base + x, at = base + j * n + i;
-        const double jj = Jref[a] + (pair_value(Jp, pos, a) + pair_value(Jp, pos, at));
-        const double kk = Kref[a] + (Kh[a] + Kh[at]);
-        if (F) F[a] = H[a] + jj - 0.5 * kk;
-        J[a] = jj;
-        K[a] = kk;
-    }
+    if (E) block_add(e, &E[m]);
 }
 
 // out = (A + A^T) / 2 (out must not alias A)
@@ -207,25 +222,6 @@ __global__ void k_delta_blockmax(int N, const double *__restrict__ D,
         unsigned long long *slot = M + (size_t)bf_shell[i] * ns + bf_shell[j];
         if (bits > *slot) atomicMax(slot, bits);
     }
-}
-
-__global__ void k_dot3_packed(MolLayout L, const double *__restrict__ A,
-                              const double *__restrict__ B, const double *__restrict__ C, double w,
-                              double *E) {
-    __shared__ double red[256];
-    const int m = blockIdx.y, n = L.n[m];
-    const size_t base = L.off[m], n2 = (size_t)n * n;
-    double acc = 0.0;
-    for (size_t x = blockIdx.x * (size_t)blockDim.x + threadIdx.x; x < n2;
-         x += (size_t)gridDim.x * blockDim.x)
-        acc += A[base + x] * (B[base + x] + (C ? C[base + x] : 0.0));
-    red[threadIdx.x] = acc;
-    __syncthreads();
-    for (int o = blockDim.x / 2; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) atomicAdd(&E[m], w * red[0]);
 }
 
 __global__ void k_pad(MolLayout L, const double *__restrict__ packed, double *padded, double diag) {
@@ -349,16 +345,15 @@ static inline dim3 grid_mol(size_t per_mol, int nmol, int z = 1) {
     return dim3((unsigned)b, (unsigned)nmol, (unsigned)z);
 }
 
-hipError_t assemble_fock_packed(const MolLayout &L, const double *Jp, const int *pos, const double *Kh,
-                                const double *H, double *F, double *J, double *K, hipStream_t s) {
-    hipLaunchKernelGGL(k_assemble_packed, grid_mol((size_t)L.nmax * L.nmax, L.nmol), dim3(256), 0,
-                       s, L, Jp, pos, Kh, H, F, J, K);
-    return hipGetLastError();
-}
-hipError_t dot3_packed(const MolLayout &L, const double *A, const double *B, const double *C,
-                       double w, double *E, hipStream_t s) {
-    hipLaunchKernelGGL(k_dot3_packed, grid_mol((size_t)L.nmax * L.nmax, L.nmol), dim3(256), 0, s,
-                       L, A, B, C, w, E);
+hipError_t assemble(const MolLayout &L, const Accum &acc, const double *H, const double *Jref,
+                    const double *Kref, double *F, double *J, double *K, const double *D, double *E,
+                    hipStream_t s) {
+    // few molecules: more blocks each (512 of them queue up little at E)
+    size_t b = ((size_t)L.nmax * L.nmax + 255) / 256;
+    const size_t most = L.nmol < 8 ? 512 / L.nmol : 64;
+    if (b > most) b = most;
+    hipLaunchKernelGGL(k_assemble, dim3((unsigned)b, (unsigned)L.nmol), dim3(256), 0, s, L, acc, H,
+                       Jref, Kref, F, J, K, D, E);
     return hipGetLastError();
 }
 hipError_t pad_blocks(const MolLayout &L, const double *packed, double *padded, double diag,
@@ -428,26 +423,19 @@ hipError_t fill_int(int *x, size_t n, int v, hipStream_t s) {
     hipLaunchKernelGGL(k_fill_int, grid_for(n), dim3(256), 0, s, x, n, v);
     return hipGetLastError();
 }
-hipError_t begin_build(double *z0, size_t n0, double *z1, size_t n1, size_t n, const int *idx,
-                       const double *src, double *dst, hipStream_t s) {
+hipError_t begin_build(double *z0, size_t n0, double *z1, size_t n1, double *z2, size_t n2,
+                       size_t n, const int *idx, const double *src, double *dst, hipStream_t s) {
     size_t most = n0 > n1 ? n0 : n1;
+    if (n2 > most) most = n2;
     if (n > most) most = n;
-    hipLaunchKernelGGL(k_begin_build, grid_for(most), dim3(256), 0, s, z0, n0, z1, n1, n, idx, src,
-                       dst);
+    hipLaunchKernelGGL(k_begin_build, grid_for(most), dim3(256), 0, s, z0, n0, z1, n1, z2, n2, n,
+                       idx, src, dst);
     return hipGetLastError();
 }
 hipError_t sum_copies2(int ncopy, size_t stride, size_t n0, const double *s0, double *d0,
                        size_t n1, const double *s1, double *d1, hipStream_t s) {
     hipLaunchKernelGGL(k_sum_copies2, grid_for(n0 + n1), dim3(256), 0, s, ncopy, stride, n0, s0,
                        d0, n1, s1, d1);
-    return hipGetLastError();
-}
-hipError_t assemble_delta(const MolLayout &L, const double *Jp, const int *pos,
-                          const double *Kh, const double *H,
-                          const double *Jref, const double *Kref, double *F, double *J, double *K,
-                          hipStream_t s) {
-    hipLaunchKernelGGL(k_assemble_delta, grid_mol((size_t)L.nmax * L.nmax, L.nmol), dim3(256), 0,
-                       s, L, Jp, pos, Kh, H, Jref, Kref, F, J, K);
     return hipGetLastError();
 }
 hipError_t symmetrize(int N, const double *A, double *out, hipStream_t s) {
