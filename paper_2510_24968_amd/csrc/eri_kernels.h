@@ -350,7 +350,8 @@ struct TileShare {
     int j0 = 0, jstep = 1;      // ket primitives of the calling lane
     __device__ __forceinline__ explicit TileShare(int t) : tile(t), lane(threadIdx.x & 63) {}
     // item of the tiles from t0 on
-    __device__ __forceinline__ TileShare(const EriArgs &a, int t0, int item) {
+    __device__ __forceinline__ TileShare(const EriArgs &a, int t0, int item) : TileShare(t0 + item) {
+        if (a.shares == 1) return;   // a tile per item: the large launches
         ls = 31 - __builtin_clz(a.ksplit);
         csplit = a.csplit;
         bstep = a.bsplit;
@@ -429,7 +430,7 @@ __device__ __forceinline__ void run_segments(const EriArgs &a, double *__restric
     for (int w = blockIdx.x; w < a.tl.nseg * a.parts; w += gridDim.x) {
         const int sg = w / a.parts, part = w - sg * a.parts;
         const int t0 = a.tl.seg_t0[sg], nt = a.tl.seg_nt[sg];
-        const int items = nt * a.csplit * a.ksplit * a.bsplit;
+        const int items = nt * a.shares;
         for (int it = wave * a.parts + part; it < items; it += wpb * a.parts)
             body(t0, __builtin_amdgcn_readfirstlane(it));
         __syncthreads();
@@ -454,7 +455,8 @@ __host__ __device__ constexpr int seg_waves(int la, int lb, int lc, int ld, int 
     return lane_min_waves(la, lb, lc, ld, ca, cdc) == 2 ? 8 : 4;
 }
 
-template <int LA, int LB, int LC, int LD, typename T, bool STORE, int CA, int CDC, bool SEG>
+template <int LA, int LB, int LC, int LD, typename T, bool STORE, int CA, int CDC, bool SEG,
+          bool SHARED = false>
 __global__ __launch_bounds__(SEG ? 64 * seg_waves(LA, LB, LC, LD, CA, CDC) : 256,
                              lane_min_waves(LA, LB, LC, LD, CA, CDC)) void k_eri_lane(EriArgs a) {
     constexpr int L = LA + LB + LC + LD, LAB = LA + LB;
@@ -564,7 +566,7 @@ __global__ __launch_bounds__(SEG ? 64 * seg_waves(LA, LB, LC, LD, CA, CDC) : 256
             constexpr int A0 = (ch / NCHCD) * CA, A1 = cmin(A0 + CA, NA);
             constexpr int CD0 = (ch % NCHCD) * CDC, CD1 = cmin(CD0 + CDC, NCD);
             constexpr int NAc = A1 - A0, NABc = NAc * NB, NCDc = CD1 - CD0;
-            if (NCHA * NCHCD > 1 && SEG && ch % sh.csplit != sh.chunk) return;
+            if (NCHA * NCHCD > 1 && SHARED && ch % sh.csplit != sh.chunk) return;
             T out[NABc][NCDc];
 #pragma unroll
             for (int x = 0; x < NABc; ++x)
@@ -713,7 +715,7 @@ __global__ __launch_bounds__(SEG ? 64 * seg_waves(LA, LB, LC, LD, CA, CDC) : 256
                     });
                 }
             } else {
-                if constexpr (SEG) share_sum(out, sh.ls);
+                if constexpr (SHARED) share_sum(out, sh.ls);
                 digest_chunk<LA, LB, LC, LD, T, A0, A1, CD0, CD1>(
                     out, D, Dk, Jb, Jk, nb, nk, Kh, N, f1, f2, f3, f4, fac, active, krow, a.kn, kl);
             }
@@ -722,7 +724,8 @@ __global__ __launch_bounds__(SEG ? 64 * seg_waves(LA, LB, LC, LD, CA, CDC) : 256
     if constexpr (SEG && !STORE) {
         double *__restrict__ krow = (double *)(stage_lds + (size_t)wpb * a.stage_bytes);
         run_segments<NA, NB>(a, krow, xoff, [&](int t0, int it) __attribute__((always_inline)) {
-            tile_body(TileShare(a, t0, it), krow, true);
+            if constexpr (SHARED) tile_body(TileShare(a, t0, it), krow, true);
+            else tile_body(TileShare(t0 + it), krow, true);
         });
     } else {
         for (int tile0 = blockIdx.x * wpb + (threadIdx.x >> 6); tile0 < ntile;
@@ -840,7 +843,7 @@ __device__ __forceinline__ void ko_tile(const EriArgs &a, const TileShare sh, co
 #pragma unroll
             for (int y = 0; y < NCDc; ++y) out[x][y] = T(0);
 
-        for (int j = sh.j0; j < nkp; j += sh.jstep) {
+        for (int j = SHARED ? sh.j0 : 0; j < nkp; j += SHARED ? sh.jstep : 1) {
             // this ket primitive, held across the bra primitives
             const double q = a.ket.p[(size_t)j * nk + ket];
             const double Kx = a.ket.P[((size_t)j * 3 + 0) * nk + ket];
@@ -851,7 +854,7 @@ __device__ __forceinline__ void ko_tile(const EriArgs &a, const TileShare sh, co
             const T *__restrict__ ekp = Sk + (size_t)j * NSK * nk + ket;
 #pragma unroll
             for (int e = EK0; e < EK1; ++e) ek[e - EK0] = ekp[(size_t)e * nk];
-            for (int i = sh.b0; i < nbp; i += sh.bstep) {
+            for (int i = SHARED ? sh.b0 : 0; i < nbp; i += SHARED ? sh.bstep : 1) {
                 const double p = rp[i * 4 + 0];
                 const double X = rp[i * 4 + 1] - Kx, Y = rp[i * 4 + 2] - Ky,
                              Z = rp[i * 4 + 3] - Kz;
@@ -1011,7 +1014,8 @@ __host__ __device__ constexpr int ko_seg_waves(int la, int lb, int lc, int ld, b
     return live <= (f64 ? 30 : 60) ? 16 : (live <= (f64 ? 60 : 90) ? 12 : 8);
 }
 
-template <int LA, int LB, int LC, int LD, typename T, bool STORE, int CA, int CDC, bool SEG>
+template <int LA, int LB, int LC, int LD, typename T, bool STORE, int CA, int CDC, bool SEG,
+          bool SHARED = false>
 __global__ __launch_bounds__(SEG ? 64 * ko_seg_waves(LA, LB, LC, LD, !std::is_same<T, float>::value)
                                  : 256)
 void k_eri_lane_ko(EriArgs a) {
@@ -1032,8 +1036,12 @@ void k_eri_lane_ko(EriArgs a) {
         const long long xoff = a.xcd_stride ? xcd_index() * a.xcd_stride : 0;
         run_segments<ncart(LA), ncart(LB)>(
             a, krow, xoff, [&](int t0, int it) __attribute__((always_inline)) {
-                ko_tile<LA, LB, LC, LD, T, STORE, CA, CDC, true>(a, TileShare(a, t0, it), bp, krow,
-                                                                 true);
+                if constexpr (SHARED)
+                    ko_tile<LA, LB, LC, LD, T, STORE, CA, CDC, true>(a, TileShare(a, t0, it), bp,
+                                                                     krow, true);
+                else
+                    ko_tile<LA, LB, LC, LD, T, STORE, CA, CDC>(a, TileShare(t0 + it), bp, krow,
+                                                               true);
             });
     } else {
         for (int tile0 = blockIdx.x * wpb + (threadIdx.x >> 6); tile0 < ntile;
@@ -1714,11 +1722,10 @@ __global__ __launch_bounds__(64) void k_eri_mfma(EriArgs a) {
 
 // Launch variants.  Variants 0..2 fix the per-lane register budget of kernel
 // A (live block + W + R^0 values; the chunking follows from it); variant 3 is
-// kernel B; variant 4 is kernel A in ket-outer order (bras with small
-// Hermite boxes: ss, ps, pp, ds; other classes run the default variant).  A budget whose chunking does not
-// fit, or needs more than MAX_CHUNKS chunks, falls back to kernel B.  The
-// autotuner picks a variant and the waves per block for every class and
-// precision.
+// kernel B; variant 4 is kernel A in ket-outer order (the classes ko_serves
+// names; others run variant 1).  A budget whose chunking does not fit, or
+// needs more than MAX_CHUNKS chunks, falls back to kernel B.  The autotuner
+// picks a variant and the waves per block for every class and precision.
 constexpr int NVARIANT = 7;
 constexpr int VARIANT_WAVE = 3;
 constexpr int VARIANT_KO = 4;
@@ -1740,17 +1747,30 @@ __host__ __device__ constexpr bool lane_fits() {
            n_chunks(LA, LB, LC, LD, BUDGET) <= MAX_CHUNKS;
 }
 
+// The widest budget at which a class has a lane kernel of its own (variant 5).
+template <int LA, int LB, int LC, int LD>
+__host__ __device__ constexpr int widest_budget() {
+    constexpr int b2 = variant_budget(2), b5 = variant_budget(VARIANT_WIDE);
+    if (!lane_fits<LA, LB, LC, LD, b2>()) return b5;
+    return lane_fits<LA, LB, LC, LD, b5>() &&
+                   n_chunks(LA, LB, LC, LD, b5) < n_chunks(LA, LB, LC, LD, b2)
+               ? b5
+               : b2;
+}
+
 // Launches of fewer than SHARE_WAVES tiles, three waves for every SIMD of the
 // GPU, are shared out until they have about as many items: by chunks first,
 // which repeat no work, then by ket primitives, then by bra primitives, which
-// repeat the digest.  Launch times summed, FP64: 3 waters 12.8 -> 0.79 ms, 10
-// waters 29.9 -> 6.1 ms, of which the kernels a class runs by default account
-// for the step to 3.2 and 9.3 ms.
+// repeat the digest (nchunk = 0: not shared out).  Launch times summed, FP64:
+// 3 waters 12.8 -> 0.79 ms, 10 waters 29.9 -> 6.1 ms, of which the kernels a
+// class runs by default account for the step to 3.2 and 9.3 ms.  The kernels
+// for it are instantiations of their own: with the loop bounds in registers
+// the large launches ran up to a quarter slower ((dp|pp) 41.7 -> 49.6 ms).
 constexpr int SHARE_WAVES = 3072;
 inline void share_tiles(EriArgs &b, int nchunk, int waves) {
     long long n = b.tl.ntile;
-    b.csplit = b.ksplit = b.bsplit = b.parts = 1;
-    if (n >= SHARE_WAVES) return;
+    b.csplit = b.ksplit = b.bsplit = b.parts = b.shares = 1;
+    if (n >= SHARE_WAVES || nchunk < 1) return;
     auto want = [&] { return (int)((SHARE_WAVES + n / 2) / n); };
     if (want() > 1) n *= b.csplit = cmin(nchunk, want());
     while (want() > 1 && b.ksplit < 8 && b.ksplit < b.ket.kmax) {
@@ -1761,6 +1781,7 @@ inline void share_tiles(EriArgs &b, int nchunk, int waves) {
     // every part of a segment keeps an item for each of its waves
     const long long per = n / b.tl.nseg / waves;
     b.parts = per > 1 ? (int)per : 1;
+    b.shares = b.csplit * b.ksplit * b.bsplit;
 }
 
 template <int LA, int LB, int LC, int LD, typename T, bool STORE>
@@ -1789,12 +1810,20 @@ void launch_mfma_kernel(int ntile, const EriArgs &a, hipStream_t s) {
 constexpr size_t LDS_PER_CU = 160 * 1024;
 
 // Segment mode of a lane-kernel launch (waves_per_block = 8 in a Fock build
-// with a.kn > 0 and a segment list): W-wave blocks over segments, the
-// dynamic LDS holding the W staging slices and the bra's K' rows.  False
-// (the caller then launches the tile-mode kernel with kn = 0) when the rows
-// do not fit next to the kernel's static LDS.
+// with a.kn > 0 and a segment list): blocks over segments, the dynamic LDS
+// holding the waves' staging slices and the bra's K' rows.  False (the
+// caller then launches the tile-mode kernel with kn = 0) when the rows do not
+// fit next to the kernel's static LDS.
+//
+// cuw: waves a CU holds by the kernel's registers.  W comes in as the most a
+// block may have and leaves as what it gets: 4 or 8 where enough such blocks
+// fit the CU's LDS to keep it as full, since the waves of a block wait for
+// each other at the end of every segment and the segments of small molecules
+// are short (1024 C/H molecules, 5.8 tiles each: 362 -> 301 ms per build, 64 of
+// them in mixed precision 44 -> 28).
 template <int LA, int LB>
-bool segment_fit(const void *kernel, int W, int nchunk, EriArgs &b, int &blocks, size_t &dyn) {
+bool segment_fit(const void *kernel, int cuw, int &W, int nchunk, EriArgs &b, int &blocks,
+                 size_t &dyn) {
     if (b.kn <= 0 || b.tl.nseg <= 0) return false;
     const size_t rows = (size_t)(ncart(LA) + ncart(LB)) * b.kn * sizeof(double);
     hipFuncAttributes fa{};
@@ -1802,8 +1831,19 @@ bool segment_fit(const void *kernel, int W, int nchunk, EriArgs &b, int &blocks,
         (void)hipGetLastError();
         return false;
     }
+    auto lds = [&](int w) { return fa.sharedSizeBytes + (size_t)w * b.stage_bytes + rows; };
+    if (lds(W) > LDS_PER_CU) return false;
+    auto held = [&](int w) { return cmin(cuw / w, (int)(LDS_PER_CU / lds(w))) * w; };
+    const int most = W;
+    int best = held(most);
+    for (int w = 4; w < most; w *= 2)
+        if (held(w) > best) best = held(w);
+    for (int w = 4; w < most; w *= 2)
+        if (held(w) == best) {
+            W = w;
+            break;
+        }
     dyn = (size_t)W * b.stage_bytes + rows;
-    if (fa.sharedSizeBytes + dyn > LDS_PER_CU) return false;
     share_tiles(b, nchunk, W);
     const long long n = (long long)b.tl.nseg * b.parts;
     blocks = n < 8192 ? (int)n : 8192;
@@ -1823,12 +1863,17 @@ void launch_budget(int ntile, int wpb, const EriArgs &a, hipStream_t s) {
         b.stage_bytes = LA == 2 ? (b.stage_prims * per_prim + 15) / 16 * 16 : 0;
         if constexpr (!STORE) {
             if (wpb == 8) {
-                constexpr int W = seg_waves(LA, LB, LC, LD, CA, CDC);
-                auto seg = k_eri_lane<LA, LB, LC, LD, T, false, CA, CDC, true>;
+                int W = seg_waves(LA, LB, LC, LD, CA, CDC);
+                // the shared form exists at the widest budget, the default's
+                constexpr bool WIDEST = BUDGET == widest_budget<LA, LB, LC, LD>();
+                const bool share = WIDEST && ntile < SHARE_WAVES;
+                auto seg = share ? k_eri_lane<LA, LB, LC, LD, T, false, CA, CDC, true, WIDEST>
+                                 : k_eri_lane<LA, LB, LC, LD, T, false, CA, CDC, true, false>;
                 int sblocks = 0;
                 size_t dyn = 0;
-                if (segment_fit<LA, LB>((const void *)seg, W, n_chunks(LA, LB, LC, LD, BUDGET), b,
-                                        sblocks, dyn)) {
+                if (segment_fit<LA, LB>((const void *)seg, W, W,
+                                        share ? n_chunks(LA, LB, LC, LD, BUDGET) : 0, b, sblocks,
+                                        dyn)) {
                     hipLaunchKernelGGL(seg, dim3(sblocks), dim3(64 * W), dyn, s, b);
                     return;
                 }
@@ -1853,13 +1898,16 @@ void launch_ko(int ntile, int wpb, const EriArgs &a, hipStream_t s) {
         b.stage_prims = b.stage_bytes = 0;
         if constexpr (!STORE) {
             if (wpb == 8) {
-                auto seg = k_eri_lane_ko<LA, LB, LC, LD, T, false, CA, CDC, true>;
-                constexpr int W = ko_seg_waves(LA, LB, LC, LD, !std::is_same<T, float>::value);
+                auto seg = ntile < SHARE_WAVES
+                               ? k_eri_lane_ko<LA, LB, LC, LD, T, false, CA, CDC, true, true>
+                               : k_eri_lane_ko<LA, LB, LC, LD, T, false, CA, CDC, true, false>;
+                int W = ko_seg_waves(LA, LB, LC, LD, !std::is_same<T, float>::value);
                 int sblocks = 0;
                 size_t dyn = 0;
                 constexpr int NCH =
                     ((ncart(LA) + CA - 1) / CA) * ((ncart(LC) * ncart(LD) + CDC - 1) / CDC);
-                if (segment_fit<LA, LB>((const void *)seg, W, NCH, b, sblocks, dyn)) {
+                const int cuw = LA + LB + LC + LD <= 1 ? 16 : W;
+                if (segment_fit<LA, LB>((const void *)seg, cuw, W, NCH, b, sblocks, dyn)) {
                     hipLaunchKernelGGL(seg, dim3(sblocks), dim3(64 * W), dyn, s, b);
                     return;
                 }
@@ -1891,13 +1939,8 @@ void launch_variant(int ntile, int variant, int wpb, const EriArgs &a, hipStream
             // ((ds|pp), (dp|pp), (dp|ds): each chunk re-evaluates Boys and
             // R, and these run at one wave per SIMD either way); every other
             // class runs variant 2
-            if constexpr (!lane_fits<LA, LB, LC, LD, variant_budget(2)>() ||
-                          (lane_fits<LA, LB, LC, LD, variant_budget(VARIANT_WIDE)>() &&
-                           n_chunks(LA, LB, LC, LD, variant_budget(VARIANT_WIDE)) <
-                               n_chunks(LA, LB, LC, LD, variant_budget(2))))
-                launch_budget<LA, LB, LC, LD, T, STORE, variant_budget(VARIANT_WIDE)>(ntile, wpb, a, s);
-            else
-                launch_budget<LA, LB, LC, LD, T, STORE, variant_budget(2)>(ntile, wpb, a, s);
+            launch_budget<LA, LB, LC, LD, T, STORE, widest_budget<LA, LB, LC, LD>()>(ntile, wpb, a,
+                                                                                     s);
             break;
         case VARIANT_MFMA:
             // the matrix-core kernel serves classes with a d bra; the others

@@ -238,10 +238,11 @@ struct EriArgs {
     // waves' staging slices.  0: every K' term is a global atomic.
     int kn;
     // launches over segments: how one tile is shared out (TileShare in
-    // eri_kernels.h) and how many blocks take a segment, all 1 for a tile per
+    // eri_kernels.h) and how many blocks (parts) take a segment, all 1 for a tile per
     // wave and a block per segment.  In the one-wave-per-quartet kernels
-    // ksplit is the number of ket ranges of a tile.
-    int csplit, ksplit, bsplit, parts;
+    // ksplit is the number of ket ranges of a tile.  shares: the product of
+    // the three.
+    int csplit, ksplit, bsplit, parts, shares;
 };
 
 

@@ -115,11 +115,11 @@ static hipError_t launch_digest(int wpb, const EriArgs &a, hipStream_t s) {
         constexpr int CA = digest_chunk_a(LA, LB, LC, LD), CDC = digest_chunk_cd(LA, LB, LC, LD);
         constexpr int NCH =
             ((ncart(LA) + CA - 1) / CA) * ((ncart(LC) * ncart(LD) + CDC - 1) / CDC);
-        int blocks = 0;
+        int blocks = 0, W = 8;
         size_t dyn = 0;
         auto seg = k_digest_stored<LA, LB, LC, LD, true>;
-        if (segment_fit<LA, LB>((const void *)seg, 8, NCH, b, blocks, dyn)) {
-            hipLaunchKernelGGL(seg, dim3(blocks), dim3(512), dyn, s, b);
+        if (segment_fit<LA, LB>((const void *)seg, 8, W, NCH, b, blocks, dyn)) {
+            hipLaunchKernelGGL(seg, dim3(blocks), dim3(64 * W), dyn, s, b);
             return hipGetLastError();
         }
     }
