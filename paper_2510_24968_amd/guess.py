@@ -353,10 +353,11 @@ class GuessNet:
         """Masked mean-square loss (device scalar) and FP32 gradients."""
         n = Xb.shape[0]
         Y, (acts, outs) = self.forward(Xb)
-        # loss and weight gradients are added up into one cleared buffer
+        # the weight gradients are added up into one cleared buffer; the loss has
+        # its own, so that a kept loss does not hold them
         sizes = [i * o for i, o in self.dims]
-        loss, *dWf = torch.zeros(1 + sum(sizes), dtype=torch.float32,
-                                 device=self.dev).split([1] + sizes)
+        dWf = torch.zeros(sum(sizes), dtype=torch.float32, device=self.dev).split(sizes)
+        loss = torch.zeros(1, dtype=torch.float32, device=self.dev)
         g = torch.empty_like(Y)
         cnt = max(float(mask.sum().item()), 1.0)
         _chk(_lib().fsim_mse(Y.numel(), _p(Y), _p(T), _p(mask), 1.0 / cnt, _p(g), _p(loss),
