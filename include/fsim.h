@@ -291,10 +291,10 @@ fsim_status fsim_get_class_profile(fsim_ctx *ctx, fsim_class_profile *out, int32
  * 3).  waves_per_block is 1, 2 or 4 for launches over tiles, every K'
  * term a global atomic (variants 3 and 6 use one block shape), or 8 for the
  * segment mode of the lane variants 0, 1, 2, 4 and 5 (see
- * fsim_set_krow_lds: blocks of 8 waves (12 or 16 for ket-outer kernels with
- * few registers), or 4 for kernels held to one wave per SIMD, over segments of
- * one bra's tiles with the bra's K' rows in LDS; launches whose rows do not fit
- * run over tiles with 4 waves per block).  Segment launches of few tiles share
+ * fsim_set_krow_lds: blocks of 4, 8, 12 or 16 waves, the fewest that fill a CU
+ * by the kernel's registers and LDS, over segments of one bra's tiles with the
+ * bra's K' rows in LDS; launches whose rows do not fit run over tiles with 4
+ * waves per block).  Segment launches of few tiles share
  * each tile out over several waves and blocks.
  * The default is variant 4 where it serves the class, variant 6 for (dd|dd) and
  * variant 5 for the rest, in segment mode with 64 tiles per segment;

@@ -281,7 +281,7 @@ static fsim_status alloc_table(DevPool &pool, PairTable &t, int l1, int l2, int 
     t.ne = n_entries(l1, l2);
     if (n == 0) return FSIM_OK;
     // one allocation per table, carved at 256-byte boundaries
-    const size_t N = n, K = kmax, NE = t.ne;
+    const size_t N = n, K = kmax, NE = t.ne, NR = n_row(l1, l2);
     const bool ko = pclass(l1, l2) <= KO_PCLASS_MAX;
     const size_t NS = ko ? K * n_scaled(l1, l2) * N : 0;
     char *base = nullptr;
@@ -304,7 +304,7 @@ static fsim_status alloc_table(DevPool &pool, PairTable &t, int l1, int l2, int 
         take(&t.E, K * NE * N);
         take(&t.Ef, K * NE * N);
         take(&t.rp, K * 4 * N);
-        take(&t.rE, K * NE * N);
+        take(&t.rE, K * NR * N);
         take(&t.rEf, K * NE * N);
         if (ko) {
             take(&t.S0, K * N);
@@ -330,7 +330,7 @@ static fsim_status build_table(fsim_ctx *c, DevPool &pool, PairTable &t, int pc,
     HIPCHK(hipMemcpy(d1, s1.data(), sizeof(int) * t.n, hipMemcpyHostToDevice));
     HIPCHK(hipMemcpy(d2, s2.data(), sizeof(int) * t.n, hipMemcpyHostToDevice));
     HIPCHK(launch_build_pairs(c->sh, t, d1, d2, nullptr));
-    HIPCHK(launch_pack_rows(t, nullptr));
+    HIPCHK(launch_pack_rows(t, c->sh, nullptr));
     HIPCHK(hipDeviceSynchronize());
     hipFree(d1);
     hipFree(d2);
@@ -1201,7 +1201,7 @@ extern "C" fsim_status fsim_schwarz_screen(fsim_ctx *c, double tau, double tau32
             HIPCHK(hipMalloc(&dq, sizeof(double) * c->nmol));
             HIPCHK(hipMemcpy(dq, Qmax.data(), sizeof(double) * c->nmol, hipMemcpyHostToDevice));
             HIPCHK(launch_prim_screen(c->kept[pc], dq, c->tau_prim, nullptr));
-            HIPCHK(launch_pack_rows(c->kept[pc], nullptr));   // the slots moved
+            HIPCHK(launch_pack_rows(c->kept[pc], c->sh, nullptr));   // the slots moved
             HIPCHK(hipDeviceSynchronize());
             hipFree(dq);
             HIPCHK(hipMemcpy(np.data(), c->kept[pc].nprim, sizeof(int) * np.size(),

@@ -735,8 +735,9 @@ __global__ __launch_bounds__(SEG ? 64 * seg_waves(LA, LB, LC, LD, CA, CDC) : 256
 }
 
 // ===========================================================================
-// Kernel A, ket-outer order (ss, ps, pp and ds bras; Fock or store mode).  The same lane-per-
-// quartet tiles as k_eri_lane, with the primitive loops swapped: each ket
+// Kernel A, ket-outer order (ss, ps, pp and ds bras, dp bras with ss and ps
+// kets; Fock or store mode).  The same lane-per-quartet tiles as k_eri_lane,
+// with the primitive loops swapped: each ket
 // primitive's data are loaded once and held in registers while the bra
 // primitives (wave-uniform, read by scalar loads from the row tables; staged
 // in LDS they cost the 64-water s/p build 312 ms against 292) run inside, and
@@ -750,8 +751,8 @@ __global__ __launch_bounds__(SEG ? 64 * seg_waves(LA, LB, LC, LD, CA, CDC) : 256
 // the norms of d components are applied to the finished block.  64 waters,
 // FP64: (pp|ps) 90.1 -> 82.7 ms, (ps|ps) 50.3 -> 46.7 ms.
 // This trades the once-per-bra-primitive bra step for one per primitive
-// quartet (cheap for small bra boxes) against loading every ket primitive
-// once per quartet instead of once per bra primitive.
+// quartet (cheap for small bra boxes, and see ko_sums) against loading every
+// ket primitive once per quartet instead of once per bra primitive.
 // ===========================================================================
 // Boys-function providers of the ket-outer tile body: the class kernels
 // stage the table of their own order L (boys.h); the persistent kernel
@@ -763,6 +764,44 @@ struct BoysTable {
     __device__ __forceinline__ void eval(double T, double *F) const { B::eval(T, tab, F); }
 };
 
+// The sums of a ps or pp bra.  With P - A = -beta AB and P - B = alpha AB,
+//   (p_i s| = S_i - AB_i S0
+//   (p_i p_j| = S_ij + delta_ij D - AB_i U_j + AB_j W_i - AB_i AB_j S0
+// where, V the Hermite integrals over the bra's indices, the sums over the
+// primitive quartets are
+//   ps: S0 = sum c beta V_0, S_i = sum c h V_i                              (4)
+//   pp: S0 = sum c alpha beta V_0, D = sum c h V_0, U_i = sum c beta h V_i,
+//       W_i = sum c alpha h V_i, S_ij = sum c h^2 V_ij                     (14)
+// so a primitive quartet takes 4 FMAs per ket component in place of the 6 of
+// the components' boxes, 14 in place of 33.  FP64 classes whose block is taken
+// in one chunk: (pp|pp) would need three chunks for its 14 x 9 sums, or two and
+// spills (46.1 -> 46.5 or 49.0 ms, 1024 C/H molecules 107 -> 126 or 113).
+// 64 waters without d shells, before and after: (pp|ps) 70.9 -> 59.6 ms, (pp|ss)
+// 23.0 -> 21.5, (ps|ps) 40.7 -> 38.9, (ps|ss) 38.8 -> 37.7.
+__host__ __device__ constexpr bool ko_sums(int la, int lb, int nchunk, bool f64) {
+    return f64 && has_factors(la, lb) && nchunk == 1;
+}
+__host__ __device__ constexpr int bra_sums(int lb) { return lb == 0 ? 4 : 14; }
+// S_ij (i <= j in the order xx xy xz yy yz zz) from 8 on
+__host__ __device__ constexpr int sum_pp(int i, int j) {
+    return i > j ? sum_pp(j, i) : 8 + i * 3 - i * (i + 1) / 2 + j;
+}
+// factor of sum k in the bra's row
+__host__ __device__ constexpr int sum_factor(int lb, int k) {
+    if (lb == 0) return k == 0 ? 0 : 1;
+    return k < 2 ? k : (k < 5 ? 2 : (k < 8 ? 3 : 4));
+}
+// Hermite index of sum k
+__host__ __device__ constexpr int sum_herm(int lb, int k) {
+    const int unit[3] = {hidx(1, 0, 0), hidx(0, 1, 0), hidx(0, 0, 1)};
+    if (lb == 0) return k == 0 ? hidx(0, 0, 0) : unit[k - 1];
+    if (k < 2) return hidx(0, 0, 0);
+    if (k < 8) return unit[(k - 2) % 3];
+    const int pair[6] = {hidx(2, 0, 0), hidx(1, 1, 0), hidx(1, 0, 1),
+                         hidx(0, 2, 0), hidx(0, 1, 1), hidx(0, 0, 2)};
+    return pair[k - 8];
+}
+
 // One tile (one bra pair x up to 64 kets) of the ket-outer kernel.
 template <int LA, int LB, int LC, int LD, typename T, bool STORE, int CA, int CDC,
           bool SHARED = false, typename BP>
@@ -771,9 +810,12 @@ __device__ __forceinline__ void ko_tile(const EriArgs &a, const TileShare sh, co
     constexpr int L = LA + LB + LC + LD, LAB = LA + LB;
     constexpr int NA = ncart(LA), NB = ncart(LB), NC = ncart(LC), ND = ncart(LD);
     constexpr int NCD = NC * ND, NHAB = nherm(LAB), NH = nherm(L);
-    constexpr int NEB = n_entries(LA, LB), NSK = n_scaled(LC, LD);
-    constexpr int NCHA = (NA + CA - 1) / CA, NCHCD = (NCD + CDC - 1) / CDC;
     constexpr bool F32 = std::is_same<T, float>::value;
+    // bra sums instead of components
+    constexpr bool SUMS = ko_sums(LA, LB, (ncart(LC) * ncart(LD) + CDC - 1) / CDC, !F32);
+    constexpr int NRB = F32 ? n_entries(LA, LB) : n_row(LA, LB), NSK = n_scaled(LC, LD);
+    constexpr int NCHA = (NA + CA - 1) / CA, NCHCD = (NCD + CDC - 1) / CDC;
+    static_assert(!SUMS || NCHA == 1, "the bra sums are for whole bras");
     const int lane = threadIdx.x & 63;
     const int tile = sh.tile;
     const T *__restrict__ Sk = stab<T>(a.ket);
@@ -828,7 +870,7 @@ __device__ __forceinline__ void ko_tile(const EriArgs &a, const TileShare sh, co
 
     // the bra's primitive rows
     const ConstPtr<double> rp = const_ptr(a.bra.rp + (size_t)bra * a.bra.kmax * 4);
-    const ConstPtr<T> re = const_ptr(rtab<T>(a.bra) + (size_t)bra * a.bra.kmax * NEB);
+    const ConstPtr<T> re = const_ptr(rtab<T>(a.bra) + (size_t)bra * a.bra.kmax * NRB);
 
     static_for<NCHA * NCHCD>([&](auto ch_) {
         constexpr int ch = decltype(ch_)::value;
@@ -837,11 +879,12 @@ __device__ __forceinline__ void ko_tile(const EriArgs &a, const TileShare sh, co
         constexpr int NAc = A1 - A0, NABc = NAc * NB, NCDc = CD1 - CD0;
         if (SHARED && NCHA * NCHCD > 1 && ch % sh.csplit != sh.chunk) return;
         constexpr int EK0 = scaled_off(LC, LD, CD0), EK1 = scaled_off(LC, LD, CD1);
-        T out[NABc][NCDc];
+        constexpr int NACC = SUMS ? bra_sums(LB) : NABc;
+        T acc[NACC][NCDc];
 #pragma unroll
-        for (int x = 0; x < NABc; ++x)
+        for (int x = 0; x < NACC; ++x)
 #pragma unroll
-            for (int y = 0; y < NCDc; ++y) out[x][y] = T(0);
+            for (int y = 0; y < NCDc; ++y) acc[x][y] = T(0);
 
         for (int j = SHARED ? sh.j0 : 0; j < nkp; j += SHARED ? sh.jstep : 1) {
             // this ket primitive, held across the bra primitives
@@ -887,7 +930,7 @@ __device__ __forceinline__ void ko_tile(const EriArgs &a, const TileShare sh, co
                 T r[NH];
                 hermite_r<L, T>(src, T(X), T(Y), T(Z), r);
                 // one ket component at a time: its ket step, then its bra step
-                const ConstPtr<T> eb = re + i * NEB;
+                const ConstPtr<T> eb = re + i * NRB + (SUMS ? row_factors(LA, LB) : 0);
                 static_for<NCDc>([&](auto cdl_) {
                     constexpr int cdl = decltype(cdl_)::value;
                     constexpr int cd = CD0 + cdl;
@@ -920,26 +963,57 @@ __device__ __forceinline__ void ko_tile(const EriArgs &a, const TileShare sh, co
                             });
                         });
                     });
-                    static_for<NABc>([&](auto abl_) {
-                        constexpr int abl = decltype(abl_)::value;
-                        constexpr int ab = (A0 + abl / NB) * NB + abl % NB;
-                        constexpr int ax = box_dim(LA, LB, ab, 0), ay = box_dim(LA, LB, ab, 1),
-                                      az = box_dim(LA, LB, ab, 2);
-                        constexpr int ao = box_off(LA, LB, ab);
-                        static_for<ax + 1>([&](auto t_) {
-                            constexpr int t = decltype(t_)::value;
-                            static_for<ay + 1>([&](auto u_) {
-                                constexpr int u = decltype(u_)::value;
-                                static_for<az + 1>([&](auto v_) {
-                                    constexpr int v = decltype(v_)::value;
-                                    constexpr int e = ao + (t * (ay + 1) + u) * (az + 1) + v;
-                                    out[abl][cdl] = fma(eb[e], V[hidx(t, u, v)], out[abl][cdl]);
+                    if constexpr (SUMS) {
+                        static_for<NACC>([&](auto k_) {
+                            constexpr int k = decltype(k_)::value;
+                            constexpr int f = sum_factor(LB, k), h = sum_herm(LB, k);
+                            acc[k][cdl] = fma(eb[f], V[h], acc[k][cdl]);
+                        });
+                    } else {
+                        static_for<NABc>([&](auto abl_) {
+                            constexpr int abl = decltype(abl_)::value;
+                            constexpr int ab = (A0 + abl / NB) * NB + abl % NB;
+                            constexpr int ax = box_dim(LA, LB, ab, 0), ay = box_dim(LA, LB, ab, 1),
+                                          az = box_dim(LA, LB, ab, 2);
+                            constexpr int ao = box_off(LA, LB, ab);
+                            static_for<ax + 1>([&](auto t_) {
+                                constexpr int t = decltype(t_)::value;
+                                static_for<ay + 1>([&](auto u_) {
+                                    constexpr int u = decltype(u_)::value;
+                                    static_for<az + 1>([&](auto v_) {
+                                        constexpr int v = decltype(v_)::value;
+                                        constexpr int e = ao + (t * (ay + 1) + u) * (az + 1) + v;
+                                        acc[abl][cdl] = fma(eb[e], V[hidx(t, u, v)], acc[abl][cdl]);
+                                    });
                                 });
                             });
                         });
-                    });
+                    }
                 });
             }
+        }
+        T out[NABc][NCDc];
+        if constexpr (SUMS) {
+            constexpr int ab0 = row_ab(LA, LB);
+            const T AB[3] = {re[ab0], re[ab0 + 1], re[ab0 + 2]};
+            static_for<NABc * NCDc>([&](auto x_) {
+                constexpr int ab = decltype(x_)::value / NCDc, y = decltype(x_)::value % NCDc;
+                constexpr int i = ab / NB, j = ab % NB;
+                if constexpr (LB == 0) {
+                    out[ab][y] = fma(-AB[i], acc[0][y], acc[1 + i][y]);
+                } else {
+                    constexpr int s2 = sum_pp(i, j);
+                    T v = acc[s2][y];
+                    if constexpr (i == j) v += acc[1][y];
+                    v = fma(AB[j], acc[5 + i][y], v);
+                    out[ab][y] = fma(-AB[i], fma(AB[j], acc[0][y], acc[2 + j][y]), v);
+                }
+            });
+        } else {
+#pragma unroll
+            for (int x = 0; x < NABc; ++x)
+#pragma unroll
+                for (int y = 0; y < NCDc; ++y) out[x][y] = acc[x][y];
         }
         if constexpr (LC == 2) {
             // the norms the scaled entries leave out (1 for s and p)
@@ -1008,8 +1082,10 @@ __host__ __device__ constexpr int ko_cdc(int la, int lb, int lc, int ld) {
 // rows for two blocks of 8.
 __host__ __device__ constexpr int ko_seg_waves(int la, int lb, int lc, int ld, bool f64) {
     const int L = la + lb + lc + ld;
-    const int live = ko_ca(la, lb, lc, ld) * ncart(lb) * ko_cdc(la, lb, lc, ld) + nherm(la + lb) +
-                     nherm(L);
+    const int cdc = ko_cdc(la, lb, lc, ld);
+    const bool sums = ko_sums(la, lb, (ncart(lc) * ncart(ld) + cdc - 1) / cdc, f64);
+    const int rows = sums ? bra_sums(lb) : ko_ca(la, lb, lc, ld) * ncart(lb);
+    const int live = rows * cdc + nherm(la + lb) + nherm(L);
     if (L <= 1) return 8;
     return live <= (f64 ? 30 : 60) ? 16 : (live <= (f64 ? 60 : 90) ? 12 : 8);
 }

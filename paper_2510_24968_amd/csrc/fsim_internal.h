@@ -135,6 +135,21 @@ __host__ __device__ constexpr int n_scaled(int l1, int l2) {
     return scaled_off(l1, l2, ncart(l1) * ncart(l2));
 }
 
+// FP64 rows of a pair: its box entries and, for ps and pp, the factors of the
+// bra sums of the ket-outer kernels (P - A = -beta AB, P - B = alpha AB,
+// beta = b/p, alpha = a/p, h = 1/(2p), c the pair's factor), from row_factors on:
+//   ps: c beta, c h, AB        pp: c alpha beta, c h, c beta h, c alpha h, c h^2, AB
+// FP32 rows hold the entries alone: the rounding of AB, the same for all
+// primitives of a pair, doubled the error of a mixed-precision build.
+__host__ __device__ constexpr bool has_factors(int l1, int l2) { return l1 == 1 && l2 <= 1; }
+__host__ __device__ constexpr int row_factors(int l1, int l2) { return n_entries(l1, l2); }
+__host__ __device__ constexpr int row_ab(int l1, int l2) {
+    return row_factors(l1, l2) + (l2 == 0 ? 2 : 5);
+}
+__host__ __device__ constexpr int n_row(int l1, int l2) {
+    return has_factors(l1, l2) ? row_ab(l1, l2) + 3 : n_entries(l1, l2);
+}
+
 __host__ __device__ constexpr int pclass(int l1, int l2) {   // l1 >= l2
     return l1 * (l1 + 1) / 2 + l2;
 }
@@ -168,8 +183,8 @@ struct PairTable {
     // the same primitive data row by row, for the bra side, where a whole
     // wave reads one pair's rows (scalar loads)
     double *rp = nullptr;                 // [n][kmax][4]: p, P
-    double *rE = nullptr;                 // [n][kmax][ne]
-    float *rEf = nullptr;                 // FP32 copy of rE
+    double *rE = nullptr;                 // [n][kmax][n_row]
+    float *rEf = nullptr;                 // [n][kmax][ne]: FP32 copies of the entries
     // scaled entries (ss, ps, pp and ds pairs, the kets of the ket-outer
     // kernels): the common factor, and every box entry but each box's last
     // divided by that last one (n_scaled per primitive pair)
@@ -272,7 +287,7 @@ hipError_t launch_pair_order(const PairTable &t, long long off, const long long 
                              const int *mol_n, int *src, int *pos, hipStream_t s);
 // Fill the row copies rp, rE, rEf and the scaled entries S0, S, Sf from the
 // columns (setup.hip).
-hipError_t launch_pack_rows(const PairTable &t, hipStream_t s);
+hipError_t launch_pack_rows(const PairTable &t, const ShellsDev &sh, hipStream_t s);
 // Drop the primitive pairs of every pair whose Schwarz bound times
 // qmax_mol[mol] is below tau_prim, compacting the slots in place (setup.hip).
 hipError_t launch_prim_screen(PairTable &t, const double *qmax_mol, double tau_prim,

@@ -184,10 +184,38 @@ __global__ void k_build_pairs(ShellsDev sh, PairTable t, const int *__restrict__
     }
 }
 
+// Value e of a ps or pp pair's row past the entries (n_row).  beta comes
+// from the rounded P, the one R^0 is taken at, so that -beta AB is P - A to its
+// last place as it is in the box entries.
+__device__ double row_factor(const PairTable &t, const ShellsDev &sh, size_t pr, size_t k, int e) {
+    const size_t n = t.n;
+    const double *A = sh.xyz + 3 * t.sh1[pr], *B = sh.xyz + 3 * t.sh2[pr];
+    const int ab0 = row_ab(t.l1, t.l2) - row_factors(t.l1, t.l2);
+    if (e >= ab0) return A[e - ab0] - B[e - ab0];
+    double ab2 = 0.0, pa = 0.0;
+    for (int d = 0; d < 3; ++d) {
+        const double ab = A[d] - B[d];
+        ab2 += ab * ab;
+        pa += (t.P[(k * 3 + d) * n + pr] - A[d]) * ab;
+    }
+    const double beta = ab2 > 0.0 ? -pa / ab2 : 0.0, alpha = 1.0 - beta;
+    const double h = 0.5 / t.p[k * n + pr];
+    // last entry of (px, s): c h, of (px, py): c h^2
+    const double last = t.E[(k * t.ne + box_off(t.l1, t.l2, t.l2 == 0 ? 1 : 2) - 1) * n + pr];
+    const double ch = t.l2 == 0 ? last : last / h;
+    switch (e) {
+        case 0: return (t.l2 == 0 ? beta : alpha * beta) * (ch / h);
+        case 1: return ch;
+        case 2: return beta * ch;
+        case 3: return alpha * ch;
+        default: return last;
+    }
+}
+
 // Row copies of the primitive data, one thread per (pair, slot, entry), the
 // four of p and P first.
-__global__ void k_pack_rows(PairTable t) {
-    const int w = t.ne + 4;
+__global__ void k_pack_rows(PairTable t, ShellsDev sh) {
+    const int nr = n_row(t.l1, t.l2), w = nr + 4;
     const size_t total = (size_t)t.n * t.kmax * w, n = t.n;
     for (size_t x = blockIdx.x * (size_t)blockDim.x + threadIdx.x; x < total;
          x += (size_t)gridDim.x * blockDim.x) {
@@ -196,11 +224,13 @@ __global__ void k_pack_rows(PairTable t) {
         const size_t pr = r / t.kmax, k = r % t.kmax;
         if (f < 4) {
             t.rp[r * 4 + f] = f == 0 ? t.p[k * n + pr] : t.P[(k * 3 + f - 1) * n + pr];
-        } else {
-            const double v = t.E[(k * t.ne + f - 4) * n + pr];
-            t.rE[r * t.ne + f - 4] = v;
-            t.rEf[r * t.ne + f - 4] = (float)v;
+            continue;
         }
+        const int e = f - 4;
+        const double v = e < t.ne ? t.E[(k * t.ne + e) * n + pr]
+                                  : row_factor(t, sh, pr, k, e - t.ne);
+        t.rE[r * nr + e] = v;
+        if (e < t.ne) t.rEf[r * t.ne + e] = (float)v;
     }
 }
 
@@ -231,11 +261,11 @@ __global__ void k_scale_entries(PairTable t) {
     }
 }
 
-hipError_t launch_pack_rows(const PairTable &t, hipStream_t s) {
+hipError_t launch_pack_rows(const PairTable &t, const ShellsDev &sh, hipStream_t s) {
     if (t.n == 0) return hipSuccess;
-    const size_t total = (size_t)t.n * t.kmax * (t.ne + 4);
+    const size_t total = (size_t)t.n * t.kmax * (n_row(t.l1, t.l2) + 4);
     const size_t b = (total + 255) / 256;
-    hipLaunchKernelGGL(k_pack_rows, dim3((unsigned)(b < 16384 ? b : 16384)), dim3(256), 0, s, t);
+    hipLaunchKernelGGL(k_pack_rows, dim3((unsigned)(b < 16384 ? b : 16384)), dim3(256), 0, s, t, sh);
     const dim3 g((t.n * t.kmax + 127) / 128);
     switch (pclass(t.l1, t.l2)) {
         case 0: hipLaunchKernelGGL((k_scale_entries<0, 0>), g, dim3(128), 0, s, t); break;
