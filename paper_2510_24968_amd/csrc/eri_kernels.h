@@ -881,10 +881,18 @@ __device__ __forceinline__ void ko_tile(const EriArgs &a, const TileShare sh, co
         constexpr int EK0 = scaled_off(LC, LD, CD0), EK1 = scaled_off(LC, LD, CD1);
         constexpr int NACC = SUMS ? bra_sums(LB) : NABc;
         T acc[NACC][NCDc];
+        auto clear = [&](T (&v)[NACC][NCDc]) __attribute__((always_inline)) {
 #pragma unroll
-        for (int x = 0; x < NACC; ++x)
+            for (int x = 0; x < NACC; ++x)
 #pragma unroll
-            for (int y = 0; y < NCDc; ++y) acc[x][y] = T(0);
+                for (int y = 0; y < NCDc; ++y) v[x][y] = T(0);
+        };
+        clear(acc);
+        // FP32: the bra primitives of a ket primitive are added up apart.  Added
+        // straight to the quartet's sum, its small terms are rounded away: K of
+        // 64 C/H molecules was off by 1.5e-12 rms, now 5.2e-13 (bra-outer kernel,
+        // which also sums in two steps, 6.3e-13).  64 waters mixed 325 -> 339 ms.
+        T part[F32 ? NACC : 1][F32 ? NCDc : 1];
 
         for (int j = SHARED ? sh.j0 : 0; j < nkp; j += SHARED ? sh.jstep : 1) {
             // this ket primitive, held across the bra primitives
@@ -897,6 +905,11 @@ __device__ __forceinline__ void ko_tile(const EriArgs &a, const TileShare sh, co
             const T *__restrict__ ekp = Sk + (size_t)j * NSK * nk + ket;
 #pragma unroll
             for (int e = EK0; e < EK1; ++e) ek[e - EK0] = ekp[(size_t)e * nk];
+            if constexpr (F32) clear(part);
+            auto &sum = [&]() -> auto & {
+                if constexpr (F32) return part;
+                else return acc;
+            }();
             for (int i = SHARED ? sh.b0 : 0; i < nbp; i += SHARED ? sh.bstep : 1) {
                 const double p = rp[i * 4 + 0];
                 const double X = rp[i * 4 + 1] - Kx, Y = rp[i * 4 + 2] - Ky,
@@ -967,7 +980,7 @@ __device__ __forceinline__ void ko_tile(const EriArgs &a, const TileShare sh, co
                         static_for<NACC>([&](auto k_) {
                             constexpr int k = decltype(k_)::value;
                             constexpr int f = sum_factor(LB, k), h = sum_herm(LB, k);
-                            acc[k][cdl] = fma(eb[f], V[h], acc[k][cdl]);
+                            sum[k][cdl] = fma(eb[f], V[h], sum[k][cdl]);
                         });
                     } else {
                         static_for<NABc>([&](auto abl_) {
@@ -983,13 +996,19 @@ __device__ __forceinline__ void ko_tile(const EriArgs &a, const TileShare sh, co
                                     static_for<az + 1>([&](auto v_) {
                                         constexpr int v = decltype(v_)::value;
                                         constexpr int e = ao + (t * (ay + 1) + u) * (az + 1) + v;
-                                        acc[abl][cdl] = fma(eb[e], V[hidx(t, u, v)], acc[abl][cdl]);
+                                        sum[abl][cdl] = fma(eb[e], V[hidx(t, u, v)], sum[abl][cdl]);
                                     });
                                 });
                             });
                         });
                     }
                 });
+            }
+            if constexpr (F32) {
+#pragma unroll
+                for (int x = 0; x < NACC; ++x)
+#pragma unroll
+                    for (int y = 0; y < NCDc; ++y) acc[x][y] += part[x][y];
             }
         }
         T out[NABc][NCDc];
@@ -1078,13 +1097,14 @@ __host__ __device__ constexpr int ko_cdc(int la, int lb, int lc, int ld) {
 // most of a CU's LDS for large molecules, so the block has as many waves as
 // the registers allow: a live set of up to 30 values runs in 128 registers
 // (16 waves, four per SIMD), up to 60 in 168 (12, three per SIMD), the rest
-// in 256 (8).  The classes of total angular momentum 0 and 1 have few enough
+// in 256 (8); FP32 kernels hold two sets of sums, of half the registers.  The
+// classes of total angular momentum 0 and 1 have few enough
 // rows for two blocks of 8.
 __host__ __device__ constexpr int ko_seg_waves(int la, int lb, int lc, int ld, bool f64) {
     const int L = la + lb + lc + ld;
     const int cdc = ko_cdc(la, lb, lc, ld);
     const bool sums = ko_sums(la, lb, (ncart(lc) * ncart(ld) + cdc - 1) / cdc, f64);
-    const int rows = sums ? bra_sums(lb) : ko_ca(la, lb, lc, ld) * ncart(lb);
+    const int rows = sums ? bra_sums(lb) : ko_ca(la, lb, lc, ld) * ncart(lb) * (f64 ? 1 : 2);
     const int live = rows * cdc + nherm(la + lb) + nherm(L);
     if (L <= 1) return 8;
     return live <= (f64 ? 30 : 60) ? 16 : (live <= (f64 ? 60 : 90) ? 12 : 8);
