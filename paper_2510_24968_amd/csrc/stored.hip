@@ -33,7 +33,7 @@ __host__ __device__ constexpr int digest_chunk_a(int la, int lb, int lc, int ld)
     return ca;
 }
 
-// SEG: segment mode as in the lane kernels (blocks of 8 waves over segments
+// SEG: segment mode as in the lane kernels (blocks of 4 or 8 waves over segments
 // of one bra's tiles, the bra's K' rows in LDS, a.kn doubles per row).
 template <int LA, int LB, int LC, int LD, bool SEG>
 __global__ __launch_bounds__(SEG ? 512 : 256) void k_digest_stored(EriArgs a) {
