@@ -1676,16 +1676,20 @@ static fsim_status fock_build_sph(fsim_ctx *c, const double *D, double *F, doubl
     return FSIM_OK;
 }
 
+// Whether a full build runs the FP64 / FP32 split lists.  A store holds FP64
+// blocks of every kept quartet in the tile order of the unsplit lists, so its
+// builds digest those in either precision.
+static bool splits_precision(const fsim_ctx *c, fsim_precision prec) {
+    return prec == FSIM_MIXED && c->tau32 > 0 && !c->stored;
+}
+
 static fsim_status fock_build(fsim_ctx *c, const double *D, double *F, double *J, double *K,
                               double *E_elec, fsim_precision prec, hipStream_t s) {
     if (!c->screened) return fail(FSIM_ESTATE, "fsim_schwarz_screen must run before a Fock build");
     if (!D) return fail(FSIM_EINVAL, "D must not be NULL");
-    if (c->sph)
-        return fock_build_sph(c, D, F, J, K, E_elec, prec == FSIM_MIXED && c->tau32 > 0 && !c->stored,
-                              s);
+    const bool mixed = splits_precision(c, prec);
+    if (c->sph) return fock_build_sph(c, D, F, J, K, E_elec, mixed, s);
     const size_t P = (size_t)c->packed;
-    // a store holds FP64 blocks of every kept quartet: its builds digest those
-    const bool mixed = prec == FSIM_MIXED && c->tau32 > 0 && !c->stored;
     if (c->profiling && c->ev.empty()) {
         c->ev.resize(2 * 2 * NPCLASS * NPCLASS);
         for (auto &e : c->ev) HIPCHK(hipEventCreate(&e));
@@ -1770,7 +1774,7 @@ extern "C" fsim_status fsim_fock_build_noalloc(fsim_ctx *c, const double *D, dou
     double *Fo = F;
     if (!Fo && E_elec) Fo = c->F;   // context-owned, allocated at create
     const AccPair acc{c->noalloc, c->noalloc + NOALLOC_MAX_PACKED};
-    STCHK(enqueue_build(c, D, Fo, J, K, prec == FSIM_MIXED && c->tau32 > 0, nullptr, s, &acc));
+    STCHK(enqueue_build(c, D, Fo, J, K, splits_precision(c, prec), nullptr, s, &acc));
     if (E_elec) STCHK(electronic_energy(c, E_elec, s));
     return FSIM_OK;
 }
