@@ -172,8 +172,9 @@ fsim_status fsim_fock_build(fsim_ctx *ctx, const double *D, double *F, double *J
  * library (2 x 2,097,152 FP64, 32 MiB, one copy per GPU, held until the
  * process ends, its address resolved at fsim_ctx_create) instead of buffers
  * the library allocates; the call itself allocates nothing (no hipMalloc,
- * no allocating library routine) and uses one shared accumulator copy, not
- * per-XCD copies.  Limit: the packed matrix size (N^2, or sum of N_m^2 for a
+ * no allocating library routine; the streams its launches overlap on were
+ * made by the screen) and uses one shared accumulator copy, not per-XCD
+ * copies.  Limit: the packed matrix size (N^2, or sum of N_m^2 for a
  * batch) must be <= 2,097,152 (N <= 1448), else FSIM_EINVAL.  Every call on
  * one GPU shares the array and clears what it uses before the build: calls
  * that overlap on one GPU (other streams, other threads, other contexts)

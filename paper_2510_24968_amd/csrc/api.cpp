@@ -157,7 +157,7 @@ struct fsim_ctx {
     // tiles per segment, per class and precision (tuning)
     int segt[NPCLASS][NPCLASS][2];
     // side streams of the class launches, joined to the build's stream
-    // before and after (created by the first build that may create them)
+    // before and after (created by the screen)
     static constexpr int NSIDE = 3;
     hipStream_t side[NSIDE] = {};
     hipEvent_t fork_ev = nullptr, join_ev[NSIDE] = {};
@@ -1096,6 +1096,32 @@ static std::vector<int> tile_starts(const std::vector<int> &lo, const std::vecto
     return st;
 }
 
+// Launches of a build: classes with tiles, per precision part (the lists of a
+// full build bound those of an incremental one).
+static int class_launches(const fsim_ctx *c, bool mixed) {
+    int n = 0;
+    for (int X = 0; X < NPCLASS; ++X)
+        for (int Y = 0; Y <= X; ++Y) {
+            const ClassLists &cl = c->lists[X][Y];
+            n += mixed ? (cl.mix64.ntile > 0) + (cl.mix32.ntile > 0) : cl.all64.ntile > 0;
+        }
+    return n;
+}
+
+// The streams and events of LaunchStreams, made by the screen so that every
+// entry point finds them: a build that may not create anything (allocation-free,
+// or under capture) overlaps its launches like any other.
+static fsim_status ensure_side_streams(fsim_ctx *c) {
+    if (c->fork_ev || std::max(class_launches(c, false), class_launches(c, true)) < 2)
+        return FSIM_OK;
+    for (int k = 0; k < fsim_ctx::NSIDE; ++k) {
+        if (!c->side[k]) HIPCHK(hipStreamCreateWithFlags(&c->side[k], hipStreamNonBlocking));
+        if (!c->join_ev[k]) HIPCHK(hipEventCreateWithFlags(&c->join_ev[k], hipEventDisableTiming));
+    }
+    HIPCHK(hipEventCreateWithFlags(&c->fork_ev, hipEventDisableTiming));
+    return FSIM_OK;
+}
+
 extern "C" fsim_status fsim_schwarz_screen(fsim_ctx *c, double tau, double tau32, double *Q_out,
                                            fsim_screen_stats *stats) {
     if (!c) return fail(FSIM_EINVAL, "ctx is NULL");
@@ -1339,6 +1365,7 @@ extern "C" fsim_status fsim_schwarz_screen(fsim_ctx *c, double tau, double tau32
         S.quartets_fp64 = S.quartets_kept;
         S.quartets_fp32 = 0;
     }
+    STCHK(ensure_side_streams(c));
     HIPCHK(hipStreamSynchronize(nullptr));   // the pair-order maps, read on any stream
     c->tau = tau;
     c->tau32 = tau32;
@@ -1393,28 +1420,6 @@ struct AccPair {
 struct DeltaRefs {
     const double *J, *K, *D;   // references, and the whole density
 };
-
-// Launches of a build: classes with tiles, per precision part (the lists of a
-// full build bound those of an incremental one).
-static int class_launches(const fsim_ctx *c, bool mixed) {
-    int n = 0;
-    for (int X = 0; X < NPCLASS; ++X)
-        for (int Y = 0; Y <= X; ++Y) {
-            const ClassLists &cl = c->lists[X][Y];
-            n += mixed ? (cl.mix64.ntile > 0) + (cl.mix32.ntile > 0) : cl.all64.ntile > 0;
-        }
-    return n;
-}
-
-static fsim_status ensure_side_streams(fsim_ctx *c, bool mixed) {
-    if (c->fork_ev || class_launches(c, mixed) < 2) return FSIM_OK;
-    for (int k = 0; k < fsim_ctx::NSIDE; ++k) {
-        if (!c->side[k]) HIPCHK(hipStreamCreateWithFlags(&c->side[k], hipStreamNonBlocking));
-        if (!c->join_ev[k]) HIPCHK(hipEventCreateWithFlags(&c->join_ev[k], hipEventDisableTiming));
-    }
-    HIPCHK(hipEventCreateWithFlags(&c->fork_ev, hipEventDisableTiming));
-    return FSIM_OK;
-}
 
 // The class launches of one build over the build's stream and the side
 // streams, each on the one with the least work so far.  A launch ends with a
@@ -1649,7 +1654,6 @@ static fsim_status fock_build_sph(fsim_ctx *c, const double *D, double *F, doubl
         c->ev.resize(2 * 2 * NPCLASS * NPCLASS);
         for (auto &e : c->ev) HIPCHK(hipEventCreate(&e));
     }
-    STCHK(ensure_side_streams(c, mixed));
     if (c->xcd_private && !c->priv) HIPCHK(c->pool.alloc(&c->priv, 2 * NXCD * (size_t)c->packed));
     std::vector<fsim_class_profile> prof;
     STCHK(enqueue_build(c, c->Dc, nullptr, c->Jc, c->Kc, mixed, c->profiling ? &prof : nullptr, s));
@@ -1694,7 +1698,6 @@ static fsim_status fock_build(fsim_ctx *c, const double *D, double *F, double *J
         c->ev.resize(2 * 2 * NPCLASS * NPCLASS);
         for (auto &e : c->ev) HIPCHK(hipEventCreate(&e));
     }
-    STCHK(ensure_side_streams(c, mixed));
     if (c->xcd_private && !c->priv) HIPCHK(c->pool.alloc(&c->priv, 2 * NXCD * P));
     const bool use_graph = c->graph_enabled && !c->profiling && !J && !K && F;
     if (use_graph) {
@@ -1989,7 +1992,6 @@ static fsim_status fock_build_delta_impl(fsim_ctx *c, const double *D, const dou
         c->ev.resize(2 * 2 * NPCLASS * NPCLASS);
         for (auto &e : c->ev) HIPCHK(hipEventCreate(&e));
     }
-    STCHK(ensure_side_streams(c, mixed));
     if (c->xcd_private && !c->priv) HIPCHK(c->pool.alloc(&c->priv, 2 * NXCD * (size_t)c->packed));
     std::vector<fsim_class_profile> prof;
     const DeltaRefs dref{Jref, Kref, D};
