@@ -461,8 +461,15 @@ fsim_status fsim_f32_to_bf16(int64_t n, const float *x, uint16_t *y, void *strea
 /* dH <- dH * [H > 0] (FP32) and, if dHb is not NULL, its BF16 copy. */
 fsim_status fsim_relu_backward(int64_t n, const float *H, float *dH, uint16_t *dHb, void *stream);
 
-/* db[j] = sum_i dY[i*m + j] for an n x m FP32 matrix. */
+/* db[j] = sum_i dY[i*m + j] for an n x m FP32 matrix, summed in a fixed order
+ * (equal inputs give equal bits). */
 fsim_status fsim_bias_grad(int32_t n, int32_t m, const float *dY, float *db, void *stream);
+
+/* The same with room for partial sums, which lets more than 2048 rows be
+ * summed by more blocks: ws holds ceil(n / 1024) * m FP32 values, or is NULL
+ * (then, and up to 2048 rows, the result is fsim_bias_grad's). */
+fsim_status fsim_bias_grad_ws(int32_t n, int32_t m, const float *dY, float *db, float *ws,
+                              void *stream);
 
 /* Masked mean-square error: *loss += sum mask (Y - T)^2 * inv_count and
  * dY = 2 mask (Y - T) inv_count (n values; loss is a device scalar). */

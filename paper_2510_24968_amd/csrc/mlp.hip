@@ -184,47 +184,56 @@ __global__ void k_relu_bwd(size_t n, const float *__restrict__ H, float *dH, uin
     }
 }
 
-// db[j] (+)= sum_i dY[i][j] over BG_SPLIT rows per block and 32 columns, 8
-// rows at a time, each read as one 128-byte line, 16 of them in flight per
-// thread; several row splits add into a cleared db.  (One block per column
-// read 4 bytes of every line on as many CUs as there are columns: 8192 x 256
-// 16 us, 32768 x 256 64 us; now 6 and 10
-// with the clearing.)
-constexpr int BG_COLS = 32, BG_ROWS = 8, BG_UNROLL = 16, BG_SPLIT = 512;
-__global__ __launch_bounds__(BG_COLS *BG_ROWS) void k_bias_grad(int n, int m,
-                                                                const float *__restrict__ dY,
-                                                                float *db) {
-    const int c = threadIdx.x % BG_COLS, r = threadIdx.x / BG_COLS;
-    const int j = blockIdx.x * BG_COLS + c;
-    float s = 0.f;
-    for (long long i0 = (long long)blockIdx.y * BG_SPLIT; j < m && i0 < n;
-         i0 += (long long)gridDim.y * BG_SPLIT) {
-        const long long i1 = n - i0 < BG_SPLIT ? n : i0 + BG_SPLIT;
-        long long i = i0 + r;
-        for (; i + (BG_UNROLL - 1) * BG_ROWS < i1; i += BG_UNROLL * BG_ROWS) {
-            float v[BG_UNROLL];
+// out[y][j] = sum of column j over the rows [y split, (y + 1) split) of dY, y =
+// blockIdx.y, in an order that depends on the rows alone, so that equal inputs
+// give equal bits: 256 partial sums of the rows r, r + 256, ..., then a tree.  A
+// thread holds the partial sums of K lanes of one column; a wave reads 64 / COLS
+// rows of COLS columns at a time, 16 or 8 loads in flight per thread.  Bound by
+// the loads of the few CUs it runs on.
+constexpr int CS_THREADS = 1024, CS_LANES = 256;
+template <int COLS>
+__global__ __launch_bounds__(CS_THREADS) void k_column_sums(int n, int m, int split,
+                                                            const float *__restrict__ dY,
+                                                            float *__restrict__ out) {
+    constexpr int RG = CS_THREADS / COLS, K = CS_LANES / RG, U = COLS == 16 ? 4 : 1;
+    const int c = threadIdx.x % COLS, r = threadIdx.x / COLS;
+    const int j = blockIdx.x * COLS + c;
+    const long long i0 = (long long)blockIdx.y * split;
+    const unsigned rows = n - i0 < split ? (unsigned)(n - i0) : (unsigned)split;
+    const float *__restrict__ p = dY + i0 * m + j;
+    float s[K];
 #pragma unroll
-            for (int u = 0; u < BG_UNROLL; ++u) v[u] = dY[(i + u * BG_ROWS) * m + j];
+    for (int k = 0; k < K; ++k) s[k] = 0.f;
+    if (j < m) {
+        unsigned i = r;
+        for (; i + (U * K - 1) * RG < rows; i += U * CS_LANES) {
+            float v[U][K];
 #pragma unroll
-            for (int u = 0; u < BG_UNROLL; ++u) s += v[u];
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int k = 0; k < K; ++k) v[u][k] = p[(size_t)(i + (u * K + k) * RG) * m];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int k = 0; k < K; ++k) s[k] += v[u][k];
         }
-        for (; i < i1; i += BG_ROWS) s += dY[i * m + j];
+        for (; i < rows; i += CS_LANES)
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+                if (i + k * RG < rows) s[k] += p[(size_t)(i + k * RG) * m];
     }
-    __shared__ float red[BG_ROWS][BG_COLS];
-    red[r][c] = s;
+#pragma unroll
+    for (int o = K / 2; o > 0; o >>= 1)
+#pragma unroll
+        for (int k = 0; k < o; ++k) s[k] += s[k + o];
+    __shared__ float red[RG][COLS];
+    red[r][c] = s[0];
     __syncthreads();
-    for (int o = BG_ROWS / 2; o > 0; o >>= 1) {
+    for (int o = RG / 2; o > 0; o >>= 1) {
         if (r < o) red[r][c] += red[r + o][c];
         __syncthreads();
     }
-    if (r == 0 && j < m) {
-        if (gridDim.y > 1) atomicAdd(&db[j], red[0][c]);
-        else db[j] = red[0][c];
-    }
-}
-__global__ void k_clear(int m, float *db) {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j < m) db[j] = 0.f;
+    if (r == 0 && j < m) out[(long long)blockIdx.y * m + j] = red[0][c];
 }
 
 // masked MSE: loss += sum mask (Y - T)^2 / count;  dY = 2 mask (Y - T) / count
@@ -457,16 +466,38 @@ extern "C" fsim_status fsim_relu_backward(int64_t n, const float *H, float *dH, 
     return hipGetLastError() == hipSuccess ? FSIM_OK : FSIM_EHIP;
 }
 
+// Up to CS_ONE_PASS rows in one launch over blocks of 16 columns, which reads a
+// matrix on few CUs (from memory, 2048 x 256: 5.7 us, 7.4 in two launches).  More
+// rows in runs of CS_SPLIT whose sums, in ws, a second launch sums (4096 x 256:
+// 7.5 us against 9.5, 8192 x 256: 7.6 against 17, 32768 x 36: 7.6 against 44),
+// with 32 columns to a block, whole cache lines (32768 x 256: 9.8 us, 14.6 with
+// 16 columns).  Without ws in one launch all the same.
+constexpr int CS_ONE_PASS = 2048, CS_SPLIT = 1024, CS_SPLITS_MAX = 32768;
+extern "C" fsim_status fsim_bias_grad_ws(int32_t n, int32_t m, const float *dY, float *db,
+                                         float *ws, void *stream) {
+    if (n <= 0 || m <= 0 || !dY || !db) return FSIM_EINVAL;
+    hipStream_t s = (hipStream_t)stream;
+    auto sums = [&](auto cols, int rows, int split, const float *x, float *out) {
+        constexpr int C = decltype(cols)::value;
+        hipLaunchKernelGGL((k_column_sums<C>), dim3((m - 1) / C + 1, (rows - 1) / split + 1),
+                           dim3(CS_THREADS), 0, s, rows, m, split, x, out);
+    };
+    const std::integral_constant<int, 16> narrow;
+    const std::integral_constant<int, 32> wide;
+    if (n <= CS_ONE_PASS || !ws) {
+        sums(narrow, n, n, dY, db);
+    } else {
+        int split = CS_SPLIT;
+        while ((n - 1) / split + 1 > CS_SPLITS_MAX) split *= 2;
+        const int ns = (n - 1) / split + 1;
+        sums(wide, n, split, dY, ws);
+        sums(wide, ns, ns, ws, db);
+    }
+    return hipGetLastError() == hipSuccess ? FSIM_OK : FSIM_EHIP;
+}
 extern "C" fsim_status fsim_bias_grad(int32_t n, int32_t m, const float *dY, float *db,
                                       void *stream) {
-    if (n <= 0 || m <= 0 || !dY || !db) return FSIM_EINVAL;
-    const int nsplit = (n - 1) / BG_SPLIT + 1;
-    const dim3 g((m + BG_COLS - 1) / BG_COLS, nsplit < 1024 ? nsplit : 1024);
-    if (g.y > 1)
-        hipLaunchKernelGGL(k_clear, dim3((m + 255) / 256), dim3(256), 0, (hipStream_t)stream, m, db);
-    hipLaunchKernelGGL(k_bias_grad, g, dim3(BG_COLS * BG_ROWS), 0, (hipStream_t)stream, n, m, dY,
-                       db);
-    return hipGetLastError() == hipSuccess ? FSIM_OK : FSIM_EHIP;
+    return fsim_bias_grad_ws(n, m, dY, db, nullptr, stream);
 }
 
 extern "C" fsim_status fsim_mse(int64_t n, const float *Y, const float *T, const float *mask,

@@ -57,6 +57,7 @@ def _lib():
             "fsim_f32_to_bf16": [i64, vp, vp, vp],
             "fsim_relu_backward": [i64, vp, vp, vp, vp],
             "fsim_bias_grad": [i32, i32, vp, vp, vp],
+            "fsim_bias_grad_ws": [i32, i32, vp, vp, vp, vp],
             "fsim_mse": [i64, vp, vp, vp, f32, vp, vp, vp],
             "fsim_adam": [i64, vp, vp, vp, vp, f32, f32, f32, f32, i32, vp, vp],
             "fsim_mlp_pack": [i32, i32, vp, vp, vp],
@@ -364,13 +365,16 @@ class GuessNet:
                              _stream()))
         gb = self.to_bf16(g)
         ks = max(1, min(64, n // 256))
+        # partial sums of the bias gradients, where more than 2048 rows use them
+        ws = torch.empty(-(-n // 1024), NHID, dtype=torch.float32, device=self.dev) \
+            if n > 2048 else None
         dW, db = [None] * 3, [None] * 3
         for k in (2, 1, 0):
             i, o = self.dims[k]
             dW[k] = dWf[k].view(i, o)
             self.gemm(i, o, n, acts[k], i, 1, gb, o, 0, C=dW[k], ksplit=ks)        # act^T g
             db[k] = torch.empty(o, dtype=torch.float32, device=self.dev)
-            _chk(_lib().fsim_bias_grad(n, o, _p(g), _p(db[k]), _stream()))
+            _chk(_lib().fsim_bias_grad_ws(n, o, _p(g), _p(db[k]), _p(ws), _stream()))
             if k > 0:
                 gp = torch.empty(n, i, dtype=torch.float32, device=self.dev)
                 self.gemm(n, i, o, gb, o, 0, self.Wb[k], o, 1, C=gp)               # g W^T
