@@ -500,13 +500,18 @@ extern "C" fsim_status fsim_bias_grad(int32_t n, int32_t m, const float *dY, flo
     return fsim_bias_grad_ws(n, m, dY, db, nullptr, stream);
 }
 
+constexpr int64_t MSE_SHARE = 256 * 36;
 extern "C" fsim_status fsim_mse(int64_t n, const float *Y, const float *T, const float *mask,
                                 float inv_count, float *dY, float *loss, void *stream) {
     if (n <= 0 || !Y || !T || !mask || !dY || !loss) return FSIM_EINVAL;
-    // every block ends in an add to the one loss word, and these queue up:
-    // 8192 x 36 values took 19 us in 1152 blocks and take 7 in 128
+    // every block ends in an add to the one loss word, and these queue up at 13 ns
+    // each, while a block streams 8 GB/s: 128 blocks to start with, then one for
+    // every MSE_SHARE values up to six to a CU.  8192 x 36 values take 5.2 us
+    // (15.5 in 1024 blocks), 131072 x 36 20.5 (44.9 in 128, 58.9 in 4096),
+    // 1048576 x 36 116 (560 in 128, 126 in 4096).
+    const int64_t most = n / MSE_SHARE < 128 ? 128 : (n / MSE_SHARE > 1536 ? 1536 : n / MSE_SHARE);
     dim3 g = grid1(n);
-    if (g.x > 128) g.x = 128;
+    if (g.x > most) g.x = (unsigned)most;
     hipLaunchKernelGGL(k_mse, g, dim3(256), 0, (hipStream_t)stream, (size_t)n, Y, T, mask,
                        inv_count, dY, loss);
     return hipGetLastError() == hipSuccess ? FSIM_OK : FSIM_EHIP;
