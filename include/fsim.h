@@ -125,7 +125,8 @@ const char *fsim_version(void);
  * symmetric orthogonaliser X = U s^-1/2 U^T, and E_nuc.  Runs on the null
  * stream and synchronises.  Errors: FSIM_EINVAL for l > 2, nprim outside
  * 1..8, exps <= 0, non-finite input, odd or out-of-range nelec, NULL
- * pointers, or an overlap matrix with an eigenvalue below 1e-10. */
+ * pointers, 2^31 or more matrix elements (sum of N_m^2) or primitive pairs of
+ * one pair class, or an overlap matrix with an eigenvalue below 1e-10. */
 fsim_status fsim_ctx_create(const fsim_basis *basis, const fsim_options *opt, fsim_ctx **out);
 
 /* Free every device and host resource of the context.  NULL is accepted. */

@@ -502,6 +502,38 @@ static fsim_status validate(const fsim_basis *b, const fsim_options *o) {
     return FSIM_OK;
 }
 
+// Matrix elements, and the primitive pairs of a pair class, are numbered by
+// 32-bit integers on the device (pair order, table kernels): contexts beyond
+// them, whose tables exceed the GPU's memory, are refused.
+static fsim_status validate_sizes(const fsim_basis *mols, int nmol) {
+    long long packed = 0, pairs[NPCLASS] = {}, kmax[NPCLASS] = {};
+    for (int m = 0; m < nmol; ++m) {
+        long long nbf = 0, ns[LMAX + 1] = {}, np[LMAX + 1] = {};
+        for (int s = 0; s < mols[m].nshell; ++s) {
+            const int l = mols[m].shell_l[s];
+            nbf += ncart_h(l);
+            ns[l]++;
+            np[l] = std::max<long long>(np[l], mols[m].shell_nprim[s]);
+        }
+        packed += nbf * nbf;
+        for (int pc = 0; pc < NPCLASS; ++pc) {
+            const int l1 = pclass_l1(pc), l2 = pclass_l2(pc);
+            pairs[pc] += l1 == l2 ? ns[l1] * (ns[l1] + 1) / 2 : ns[l1] * ns[l2];
+            kmax[pc] = std::max(kmax[pc], np[l1] * np[l2]);
+        }
+    }
+    constexpr long long most = 0x7fffffffLL;
+    if (packed > most)
+        return fail(FSIM_EINVAL, "the packed matrix size " + std::to_string(packed) +
+                                     " exceeds 2^31 - 1 elements");
+    for (int pc = 0; pc < NPCLASS; ++pc)
+        if (pairs[pc] * kmax[pc] > most)
+            return fail(FSIM_EINVAL, "a pair class of " + std::to_string(pairs[pc]) + " pairs of " +
+                                         std::to_string(kmax[pc]) +
+                                         " primitive pairs exceeds 2^31 - 1");
+    return FSIM_OK;
+}
+
 static fsim_status batched_orthogonaliser(fsim_ctx *c, hipStream_t s);
 
 // Classes the ket-outer kernel serves: ss, ps, pp and ds bras, dp bras with
@@ -532,6 +564,7 @@ static fsim_status create_impl(const fsim_basis *mols, int nmol, const fsim_opti
             return v;
         }
     }
+    if (fsim_status v = validate_sizes(mols, nmol); v != FSIM_OK) return v;
     fsim_ctx *c = new fsim_ctx();
     auto cleanup = [&](fsim_status st) {
         fsim_ctx_destroy(c);
