@@ -1429,7 +1429,6 @@ static void drop_graphs(fsim_ctx *c) {
 }
 
 static constexpr int NXCD = 8;   // XCDs of an MI355X
-static constexpr size_t ASSEMBLE_COPIES_MAX = 1 << 14;
 
 // Persistent queue slots (as persistent.hip orders them) and the class record
 // the profile uses for the persistent launch.
@@ -1591,6 +1590,9 @@ static fsim_status enqueue_build(fsim_ctx *c, const double *D, double *F, double
                 const int f32 = mixed && part == 1;
                 const ListStats &st = mixed ? (part == 0 ? cl.sm64 : cl.sm32) : cl.s64;
                 // a launch costs at least its latency, some 1e8 of these operations
+                // (1 water 192 us without that term, 183 with it, 3 waters 496 and 486,
+                // on one stream 433 and 708; 10 waters and the batches within 3% of
+                // each other from 0 to launches dealt out in turn)
                 hipStream_t sl = ls.next(st.flops_exec + 1e8);
                 if (c->stored && !dref) {
                     a.out = c->store + c->store_off[X][Y];
@@ -1652,15 +1654,10 @@ static fsim_status enqueue_build(fsim_ctx *c, const double *D, double *F, double
         HIPCHK(launch_persistent(mixed && part == 1, q, s));
         if (prof) HIPCHK(hipEventRecord(c->ev[nev++], s));
     }
-    // the copies of small matrices are summed by the assembly itself (it reads
-    // every element twice)
-    Accum sums{Jsum, Ksum, c->pj_pos, 1, 0};
-    if (xp && P <= ASSEMBLE_COPIES_MAX)
-        sums = Accum{c->priv, c->priv + NXCD * P, c->pj_pos, NXCD, P};
-    else if (xp)
+    if (xp)
         HIPCHK(sum_copies2(NXCD, P, PJ, c->priv, Jsum, P, c->priv + NXCD * P, Ksum, s));
-    HIPCHK(assemble(layout_of(c), sums, c->H, dref ? dref->J : nullptr, dref ? dref->K : nullptr, F,
-                    J, K, De, F ? c->Emol : nullptr, s));
+    HIPCHK(assemble(layout_of(c), Accum{Jsum, Ksum, c->pj_pos}, c->H, dref ? dref->J : nullptr,
+                    dref ? dref->K : nullptr, F, J, K, De, F ? c->Emol : nullptr, s));
     return FSIM_OK;
 }
 

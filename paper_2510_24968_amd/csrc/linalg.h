@@ -37,14 +37,11 @@ struct MolLayout {
     const long long *off = nullptr;   // [nmol]
     const int *n = nullptr;           // [nmol]
 };
-// J' and K' half-sums of a build: ncopy copies of each, stride elements
-// apart; J' in pair order (J' of matrix element x is J[pos[x]], 0 where
-// pos[x] < 0).
+// J' and K' half-sums of a build; J' in pair order (J' of matrix element x is
+// J[pos[x]], 0 where pos[x] < 0).
 struct Accum {
     const double *J = nullptr, *K = nullptr;
     const int *pos = nullptr;
-    int ncopy = 1;
-    size_t stride = 0;
 };
 // per block: J = Jref + J' + J'^T, K = Kref + K' + K'^T (no references: NULL;
 // J may alias Jref, K may alias Kref), F = H + J - K/2, and E[m] += 1/2

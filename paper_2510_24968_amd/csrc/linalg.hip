@@ -18,8 +18,7 @@ __global__ void k_fill_int(int *x, size_t n, int v) {
 // Start of a Fock build: the accumulators and the energies cleared and the
 // density gathered into pair order, in one launch (a small molecule's build is
 // a few launches of some 5 us each: 8 H atoms 93 -> 74 us with this and
-// k_sum_copies2, 46 -> 39 us with the energy and, for small matrices, the
-// copy sums taken into the assembly).
+// k_sum_copies2, 46 -> 37 us with the energy taken into the assembly).
 __global__ void k_begin_build(double *z0, size_t n0, double *z1, size_t n1, double *z2, size_t n2,
                               size_t n, const int *__restrict__ idx,
                               const double *__restrict__ src, double *__restrict__ dst) {
@@ -32,7 +31,9 @@ __global__ void k_begin_build(double *z0, size_t n0, double *z1, size_t n1, doub
 }
 
 // dst[i] = sum of ncopy copies of src, for the J' (n0 elements) and K' (n1)
-// accumulators in one launch.
+// accumulators in one launch.  (The assembly, which reads every element twice,
+// is no place for these sums, however small the matrix: 8 H atoms 36.7 -> 37.1
+// us, 32 of them 103.7 -> 106.3, 3 waters 478 -> 489.)
 __global__ void k_sum_copies2(int ncopy, size_t stride, size_t n0, const double *__restrict__ s0,
                               double *__restrict__ d0, size_t n1, const double *__restrict__ s1,
                               double *__restrict__ d1) {
@@ -47,21 +48,11 @@ __global__ void k_sum_copies2(int ncopy, size_t stride, size_t n0, const double 
     }
 }
 
-// Sum of element x over the copies of an accumulator.
-__device__ __forceinline__ double copies_sum(const double *__restrict__ A, int ncopy,
-                                             size_t stride, size_t x) {
-    double v = A[x];
-    for (int k = 1; k < ncopy; ++k) v += A[k * stride + x];
-    return v;
-}
 // J' of matrix element x from the pair-ordered sums: 0 where x names no
 // stored element (a dropped pair, or the transpose of a stored one).
 __device__ __forceinline__ double pair_value(const Accum &acc, size_t x) {
     const int o = acc.pos[x];
-    return o >= 0 ? copies_sum(acc.J, acc.ncopy, acc.stride, o) : 0.0;
-}
-__device__ __forceinline__ double k_value(const Accum &acc, size_t x) {
-    return copies_sum(acc.K, acc.ncopy, acc.stride, x);
+    return o >= 0 ? acc.J[o] : 0.0;
 }
 // *E += the block's sum of v
 __device__ __forceinline__ void block_add(double v, double *E) {
@@ -165,7 +156,7 @@ __global__ void k_assemble(MolLayout L, Accum acc, const double *__restrict__ H,
         const size_t i = x / n, j = x - i * n;
         const size_t a = base + x, at = base + j * n + i;
         double jj = pair_value(acc, a) + pair_value(acc, at);
-        double kk = k_value(acc, a) + k_value(acc, at);
+        double kk = acc.K[a] + acc.K[at];
         if (Jref) {
             jj = Jref[a] + jj;
             kk = Kref[a] + kk;
